@@ -106,7 +106,7 @@ __host__ __device__ constexpr int scr_words_of(int groups, int var) { return var
 __device__ __forceinline__ uint32_t swizzle4(uint32_t a) { return a ^ ((a >> 6) & 0xFCu); }
 
 struct SegInfo {
-  uint32_t gstart;   // first group of the segment in the values/runs arrays
+  uint32_t base;     // array position minus flat position: flat group f of the segment is group base + f (mod 2^32)
   uint32_t off;      // first group of the segment in the workgroup's flat sequence
   uint32_t cnt;      // groups in the segment (> 0)
   float xs;          // x_k * 2^s (s: the workgroup's fixed-point scale)
@@ -122,6 +122,14 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same for the compiler alone: a wavefront's LDS operations complete in
+// order, so a read issued after a write sees it without a wait between them.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "singlethread");
 }
 
 // The same pattern with max: lane 63 ends with the wavefront maximum.
@@ -225,7 +233,7 @@ __device__ __forceinline__ int group_span4(uint32_t rw) {
 // a whole wavefront: the n_seg <= 64 * 64 segments, sorted by offset, are
 // searched with two ballots, over every stride-th segment and then over the
 // one bucket of stride segments that holds `at`.  Returns the segment's index
-// and its gstart, off and cnt (wavefront-uniform; xs is left 0).
+// and its base, off and cnt (wavefront-uniform; xs is left 0).
 __device__ __forceinline__ int holding_segment(const SegInfo* seg, int n_seg, uint32_t at, int lane, SegInfo& r) {
   const int stride = (n_seg + kWave - 1) / kWave;   // <= 64
   const int s1 = min(lane * stride, n_seg - 1);
@@ -234,7 +242,7 @@ __device__ __forceinline__ int holding_segment(const SegInfo* seg, int n_seg, ui
   const int hi = min(c1 * stride, n_seg);
   const SegInfo sg = seg[min(lo + lane, n_seg - 1)];
   const int c2 = __popcll(__ballot(lo + lane < hi && sg.off <= at));   // >= 1
-  r.gstart = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.gstart), c2 - 1));
+  r.base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.base), c2 - 1));
   r.off = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.off), c2 - 1));
   r.cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.cnt), c2 - 1));
   r.xs = 0.f;
@@ -285,7 +293,6 @@ template <int G>
 struct Pass {
   uint4 v[G];        // 8 fp16 values per group
   uint32_t rw[G];    // 8 packed 4-bit runs per group
-  uint4 rr[G];       // 8 16-bit row offsets per group (16-bit row layout)
   int hpos[G];       // flat position of the group's segment head relative to the pass start (< 0: earlier)
   float xs[G];       // scaled x_k of the group's column
   uint32_t live;     // bit i: group i holds data
@@ -299,7 +306,7 @@ struct Pass {
 // assignment and has every lane idle.  scr holds 64*G ints per wavefront:
 // segment heads are tagged with a negative value unique to the pass (the
 // accumulation step stores non-negative prefix sums in the same array).
-template <int G, bool ROWS16>
+template <int G>
 __device__ __forceinline__ void fetch_pass(Pass<G>& a, const Streams& st, const SegInfo* seg, int* scr,
                                            uint32_t pb, int icur, int i_end, uint32_t pe, int lane) {
   constexpr uint32_t P = kWave * G;
@@ -344,7 +351,7 @@ __device__ __forceinline__ void fetch_pass(Pass<G>& a, const Streams& st, const 
       const bool lv = f < pe;
       a.hpos[i] = static_cast<int>(si.off) - static_cast<int>(pb);
       a.xs[i] = si.xs;
-      gl[i] = lv ? si.gstart + (f - si.off) : 0u;
+      gl[i] = lv ? si.base + f : 0u;
       a.live |= (lv ? 1u : 0u) << i;
       end = si.off + si.cnt;
     }
@@ -360,12 +367,7 @@ __device__ __forceinline__ void fetch_pass(Pass<G>& a, const Streams& st, const 
   for (int i = 0; i < G; ++i) {
     const auto v = __builtin_amdgcn_raw_buffer_load_b128(st.values, static_cast<int>(gl[i] << 4), 0, kStreamPolicy);
     a.v[i] = make_uint4(v[0], v[1], v[2], v[3]);
-    if constexpr (ROWS16) {
-      const auto r = __builtin_amdgcn_raw_buffer_load_b128(st.runs, static_cast<int>(gl[i] << 4), 0, kStreamPolicy);
-      a.rr[i] = make_uint4(r[0], r[1], r[2], r[3]);
-    } else {
-      a.rw[i] = __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>(gl[i] << 2), 0, 0);
-    }
+    a.rw[i] = __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>(gl[i] << 2), 0, 0);
   }
 }
 
@@ -395,13 +397,13 @@ __device__ __forceinline__ uint32_t add_byte(uint32_t a, uint32_t b) {
   return r;
 }
 
-// Adds entry j's product at LDS byte address a + 4 * (j + 1), the constant in
+// Adds entry j's product at LDS byte address a + 4 * j, the constant in
 // the instruction's offset field.  (LDS operations complete in order, so the
 // compiler's waits for its own LDS accesses stay correct around this one; the
 // clobber keeps it in order with them.)
 template <int J>
 __device__ __forceinline__ void tile_add(uint32_t a, int v) {
-  asm volatile("ds_add_u32 %0, %1 offset:%2" : : "v"(a), "v"(v), "i"(4 * (J + 1)) : "memory");
+  asm volatile("ds_add_u32 %0, %1 offset:%2" : : "v"(a), "v"(v), "i"(4 * J) : "memory");
 }
 // The same at LDS byte address a exactly.
 __device__ __forceinline__ void tile_add_at(uint32_t a, int v) {
@@ -435,7 +437,7 @@ __device__ __forceinline__ uint32_t min_u16x2(uint32_t w, uint32_t c) {
 // constant 4 * (j + 1) is an immediate.  Returns the
 // segment-relative sum of 4 * (run + 1) through lane 63's last group (the
 // carry when that segment goes on into the next pass), wavefront-uniform.
-template <int G, bool SWZ>
+template <int G>
 __device__ __forceinline__ int accumulate_pass(const Pass<G>& a, int carry4, int base4_cap, uint32_t tile_lds,
                                                int* scr, int lane) {
   uint32_t R4e[G], R4o[G];
@@ -464,35 +466,10 @@ __device__ __forceinline__ int accumulate_pass(const Pass<G>& a, int carry4, int
     const int Y = X + C4[i];
     const int at_head = scr[max(a.hpos[i], 0)];
     const int rel4 = a.hpos[i] >= 0 ? Y - at_head : Y + carry4;   // segment-relative
-    // entry j lands at base4 + sum_{i<=j} 4 r_i + 4 (j + 1) with base4 >= -4;
-    // the cap keeps even a corrupt stream inside the tile's slack
-    const uint32_t base4 = static_cast<uint32_t>(min(rel4 - 4, base4_cap)) + (SWZ ? 0u : tile_lds);
-    if constexpr (SWZ) {
-      if ((a.live >> i) & 1u) {
-        // the running offset is tile-relative and advances by 4 (r_j + 1)
-        // (each byte at most 64, so adding 4 per byte cannot carry); the
-        // slot order is applied to it, then the tile's address added
-        const float xs = a.xs[i];
-        const uint32_t E = R4e[i] + 0x04040404u, O = R4o[i] + 0x04040404u;
-        uint32_t ad = base4;
-        ad = add_byte<0>(ad, E);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v[i].x, xs)));
-        ad = add_byte<0>(ad, O);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v[i].x, xs)));
-        ad = add_byte<1>(ad, E);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v[i].y, xs)));
-        ad = add_byte<1>(ad, O);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v[i].y, xs)));
-        ad = add_byte<2>(ad, E);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v[i].z, xs)));
-        ad = add_byte<2>(ad, O);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v[i].z, xs)));
-        ad = add_byte<3>(ad, E);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v[i].w, xs)));
-        ad = add_byte<3>(ad, O);
-        tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v[i].w, xs)));
-      }
-    } else if ((a.live >> i) & 1u) {
+    // entry j lands at base4 + sum_{i<=j} 4 r_i + 4 j; the cap keeps even a
+    // corrupt stream inside the tile's slack
+    const uint32_t base4 = static_cast<uint32_t>(min(rel4, base4_cap + 4)) + tile_lds;
+    if ((a.live >> i) & 1u) {
       const float xs = a.xs[i];
       uint32_t ad = base4;
       ad = add_byte<0>(ad, R4e[i]);
@@ -517,26 +494,217 @@ __device__ __forceinline__ int accumulate_pass(const Pass<G>& a, int carry4, int
   return __builtin_amdgcn_readlane(tail, kWave - 1);
 }
 
+// ---- one group per lane ---------------------------------------------------
+// The segments of a pass are found from head bits: one bit per flat position,
+// set where a segment starts.  A wavefront builds them for kHeadPasses passes
+// at a time in its scratch (one LDS atomic per segment) and keeps them in one
+// register, lane l holding 32 positions, so a pass costs two v_readlane and
+// two v_mbcnt to give every lane its segment, and the segment of the next
+// pass and whether a segment goes on into it are scalar.  Lanes past the
+// range repeat its last group (no traffic of their own) and add nothing.
+//
+// What bounds a product here is the chain of latencies in a wavefront, not
+// instruction issue: a wavefront of the LLM shapes walks 1 to 40 passes, so
+// passes that are set up and not used count as much as the work.  Hence no
+// pass is set up after the walk's last round (a walk of n passes sets up n
+// rounded up to the ring's depth; twice the depth more cost 4 to 8 % up to
+// 11 MB per product), the LDS reads of the ring's first passes are issued
+// together, and a later pass's read passes while an earlier one is decoded.
+// Against the walk that the kernels with several groups per lane keep (a tag
+// written and read back through LDS per pass, a select per idle lane), us per
+// product in a graph of 60, three matrices in turn: 700 x 513 4.39 -> 3.99,
+// 4096 x 4096 ws 70 as 70 5.13 -> 4.70, 5120 x 5120 60/60 6.50 -> 6.07,
+// 4096 x 11008 50/50 11.06 -> 10.91, 28672 x 8192 50/40 32.4 -> 32.1 (there
+// HBM bounds it: a plain read of its bytes takes 26.9), two 11008 x 4096
+// 50/50 in one launch 16.8 -> 15.7.
+constexpr int kHeadPasses = 30;   // of the 32 that 64 words hold: a multiple of either ring depth
+
+struct Pass1 {
+  uint4 v;           // 8 fp16 values
+  uint32_t rw;       // their 8 packed 4-bit runs
+  uint4 rr;          // their 16-bit row offsets (16-bit row layout)
+  int hpos4;         // 4 * (flat position of the segment's head - the pass's start); < 0: earlier
+  float xs;          // scaled x_k of the group's column
+  bool cont;         // the pass's last segment goes on into the next pass (wavefront-uniform)
+};
+
+// Marks a segment that starts at flat position off, in (pb, pb + span].
+__device__ __forceinline__ bool mark_head(int* scr, uint32_t off, uint32_t pb, uint32_t span) {
+  const uint32_t i = off - pb - 1u;
+  if (i < span) __hip_atomic_fetch_or(scr + (i >> 5), 1 << (i & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  return i < span;
+}
+
+// Bit i of lane l's word: a segment starts at flat position pb + 1 + 32 l + i,
+// below pe (pb < pe).  Segments j0 and later are looked at (those before it
+// are marked or do not start after pb), if there are any left to mark.  The
+// scratch is zero before the first mark and again on return.
+__device__ __forceinline__ uint32_t head_bits(const SegInfo* seg, int n_seg, int* scr, uint32_t pb, int j0, bool more,
+                                              uint32_t span, int lane) {
+  if (more) {
+    for (int j = j0 + lane;; j += kWave) {
+      bool in = false;
+      if (j < n_seg) in = mark_head(scr, seg[j].off, pb, span);
+      if (__ballot(in) != ~0ull) break;   // offsets ascend: the rest starts later
+    }
+  }
+  wave_lds_order();
+  const uint32_t w = static_cast<uint32_t>(scr[lane]);
+  wave_lds_order();
+  scr[lane] = 0;   // for the next call
+  wave_lds_order();
+  return w;
+}
+
+// Start of the walk of [pb0, pe): the segment that holds pb0 (its index is
+// returned, its fields in s0) and the head bits from there.  The search is
+// holding_segment's; with at most 64 segments its second look suffices, and
+// the segments that it reads are marked without reading them again.
+__device__ __forceinline__ int start_walk(const SegInfo* seg, int n_seg, int* scr, uint32_t pb0, uint32_t pe, int lane,
+                                          SegInfo& s0, uint32_t& hw) {
+  int lo = 0, hi = n_seg;
+  if (n_seg > kWave) {
+    const int stride = (n_seg + kWave - 1) / kWave;   // <= 64
+    const int c1 = __popcll(__ballot(seg[min(lane * stride, n_seg - 1)].off <= pb0));   // >= 1: segment 0 starts at 0
+    lo = min((c1 - 1) * stride, n_seg - 1);
+    hi = min(c1 * stride, n_seg);
+  }
+  const SegInfo sg = seg[min(lo + lane, n_seg - 1)];
+  const uint32_t span = min(pe - pb0 - 1u, 32u * kWave);
+  if (lo + lane < n_seg) mark_head(scr, sg.off, pb0, span);
+  const int c2 = __popcll(__ballot(lo + lane < hi && sg.off <= pb0));   // >= 1
+  s0.base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.base), c2 - 1));
+  s0.off = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.off), c2 - 1));
+  s0.cnt = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.cnt), c2 - 1));
+  s0.xs = 0.f;
+  const uint32_t last = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sg.off), kWave - 1));
+  hw = head_bits(seg, n_seg, scr, pb0, lo + kWave, lo + kWave < n_seg && last <= pb0 + span, span, lane);
+  return lo + c2 - 1;
+}
+
+// Gives each lane the segment of its group in the pass from flat position pb.
+// hw: the head bits, whose words wi and wi + 1 are this pass's.  icur: the
+// segment holding pb, advanced to the one that holds the next pass's start.
+struct Look1 {
+  uint32_t base, off;
+  float xs;
+  bool cont;
+};
+__device__ __forceinline__ Look1 look_pass1(const SegInfo* seg, uint32_t hw, int wi, int& icur) {
+  const uint32_t m0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hw), wi));
+  const uint32_t m1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hw), wi + 1));
+  const uint32_t sid = __builtin_amdgcn_mbcnt_hi(m1, __builtin_amdgcn_mbcnt_lo(m0, static_cast<uint32_t>(icur)));
+  const SegInfo si = seg[sid];
+  icur += __popc(m0) + __popc(m1);
+  return Look1{si.base, si.off, si.xs, (m1 >> 31) == 0u};
+}
+
+// Issues the loads of the pass from flat position pb (the policies are
+// fetch_pass's).  A pass past the range reads past the arrays: zeros, and no
+// traffic.
+template <bool ROWS16>
+__device__ __forceinline__ void load_pass1(Pass1& a, const Look1& k, const Streams& st, uint32_t pb, uint32_t pe, int lane) {
+  const uint32_t gl = k.base + min(pb + static_cast<uint32_t>(lane), pe - 1u);
+  a.hpos4 = static_cast<int>((k.off << 2) - (pb << 2));
+  a.xs = k.xs;
+  a.cont = k.cont;
+  const uint32_t idle = pb < pe ? 0u : 0x80000000u;
+  const int off16 = static_cast<int>((gl << 4) | idle);
+  const auto v = __builtin_amdgcn_raw_buffer_load_b128(st.values, off16, 0, kStreamPolicy);
+  a.v = make_uint4(v[0], v[1], v[2], v[3]);
+  if constexpr (ROWS16) {
+    const auto r = __builtin_amdgcn_raw_buffer_load_b128(st.runs, off16, 0, kStreamPolicy);
+    a.rr = make_uint4(r[0], r[1], r[2], r[3]);
+  } else {
+    a.rw = __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((gl << 2) | idle), 0, 0);
+  }
+  // the passes' loads stay in order, so that the wait for one leaves the later ones in flight
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Decodes one pass of n_live groups and adds its products into the tile (row
+// arithmetic on byte offsets, as in accumulate_pass).  carry4: 4 * sum of
+// (run + 1) over the earlier groups of the segment that holds the pass's
+// start (0 at a head).  Returns the same through the pass's last group.
+template <bool SWZ>
+__device__ __forceinline__ int accumulate_pass1(const Pass1& a, int carry4, int base4_cap, uint32_t tile_lds,
+                                                uint32_t n_live, int lane) {
+  const uint32_t rw = a.rw;
+  // 4 * sum of (run + 1): one dot product of the nibbles with 4
+  const int S4 = static_cast<int>(__builtin_amdgcn_udot8(rw, 0x44444444u, 32u, false));
+  const int incl = wave_inclusive_scan(S4);
+  const int X = incl - S4 + carry4;   // before the group, from the pass's start
+  const int at_head = __builtin_amdgcn_ds_bpermute(a.hpos4, X);
+  const int rel4 = X - (a.hpos4 >= 0 ? at_head : 0);   // segment-relative
+  // entry j lands at rel4 + sum_{i<=j} 4 r_i + 4 j; the cap keeps even a
+  // corrupt stream inside the tile's slack
+  const uint32_t base4 = min(static_cast<uint32_t>(rel4), static_cast<uint32_t>(base4_cap + 4)) + (SWZ ? 0u : tile_lds);
+  if (static_cast<uint32_t>(lane) < n_live) {
+    const uint32_t R4e = (rw << 2) & 0x3C3C3C3Cu;   // byte k: 4 * r_{2k}
+    const uint32_t R4o = (rw >> 2) & 0x3C3C3C3Cu;   // byte k: 4 * r_{2k+1}
+    const float xs = a.xs;
+    if constexpr (SWZ) {
+      // the running offset is tile-relative and advances by 4 (r_j + 1)
+      // (each byte at most 64, so adding 4 per byte cannot carry); the
+      // slot order is applied to it, then the tile's address added
+      const uint32_t E = R4e + 0x04040404u, O = R4o + 0x04040404u;
+      uint32_t ad = base4 - 4u;
+      ad = add_byte<0>(ad, E);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v.x, xs)));
+      ad = add_byte<0>(ad, O);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v.x, xs)));
+      ad = add_byte<1>(ad, E);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v.y, xs)));
+      ad = add_byte<1>(ad, O);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v.y, xs)));
+      ad = add_byte<2>(ad, E);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v.z, xs)));
+      ad = add_byte<2>(ad, O);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v.z, xs)));
+      ad = add_byte<3>(ad, E);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_lo_f16(a.v.w, xs)));
+      ad = add_byte<3>(ad, O);
+      tile_add_at(swizzle4(ad) + tile_lds, round_to_fixed(mul_hi_f16(a.v.w, xs)));
+    } else {
+      uint32_t ad = base4;
+      ad = add_byte<0>(ad, R4e);
+      tile_add<0>(ad, round_to_fixed(mul_lo_f16(a.v.x, xs)));
+      ad = add_byte<0>(ad, R4o);
+      tile_add<1>(ad, round_to_fixed(mul_hi_f16(a.v.x, xs)));
+      ad = add_byte<1>(ad, R4e);
+      tile_add<2>(ad, round_to_fixed(mul_lo_f16(a.v.y, xs)));
+      ad = add_byte<1>(ad, R4o);
+      tile_add<3>(ad, round_to_fixed(mul_hi_f16(a.v.y, xs)));
+      ad = add_byte<2>(ad, R4e);
+      tile_add<4>(ad, round_to_fixed(mul_lo_f16(a.v.z, xs)));
+      ad = add_byte<2>(ad, R4o);
+      tile_add<5>(ad, round_to_fixed(mul_hi_f16(a.v.z, xs)));
+      ad = add_byte<3>(ad, R4e);
+      tile_add<6>(ad, round_to_fixed(mul_lo_f16(a.v.w, xs)));
+      ad = add_byte<3>(ad, R4o);
+      tile_add<7>(ad, round_to_fixed(mul_hi_f16(a.v.w, xs)));
+    }
+  }
+  return __builtin_amdgcn_readlane(rel4 + S4, kWave - 1);
+}
+
 // 16-bit row layout: each entry's row offset is loaded, so there is nothing
 // to reconstruct.  Offsets are clamped to R + 7 (the tile's slack), four
 // times each (4 * (R + 7) < 2^16), and added to the tile's address per entry.
-template <int G>
-__device__ __forceinline__ void accumulate_pass_rows16(const Pass<G>& a, uint32_t cap_rows2, uint32_t tile_lds) {
-#pragma unroll
-  for (int i = 0; i < G; ++i) {
-    if ((a.live >> i) & 1u) {
-      const float xs = a.xs[i];
-      const uint32_t r0 = min_u16x2(a.rr[i].x, cap_rows2) << 2, r1 = min_u16x2(a.rr[i].y, cap_rows2) << 2;
-      const uint32_t r2 = min_u16x2(a.rr[i].z, cap_rows2) << 2, r3 = min_u16x2(a.rr[i].w, cap_rows2) << 2;
-      tile_add_at(add_word<0>(tile_lds, r0), round_to_fixed(mul_lo_f16(a.v[i].x, xs)));
-      tile_add_at(add_word<1>(tile_lds, r0), round_to_fixed(mul_hi_f16(a.v[i].x, xs)));
-      tile_add_at(add_word<0>(tile_lds, r1), round_to_fixed(mul_lo_f16(a.v[i].y, xs)));
-      tile_add_at(add_word<1>(tile_lds, r1), round_to_fixed(mul_hi_f16(a.v[i].y, xs)));
-      tile_add_at(add_word<0>(tile_lds, r2), round_to_fixed(mul_lo_f16(a.v[i].z, xs)));
-      tile_add_at(add_word<1>(tile_lds, r2), round_to_fixed(mul_hi_f16(a.v[i].z, xs)));
-      tile_add_at(add_word<0>(tile_lds, r3), round_to_fixed(mul_lo_f16(a.v[i].w, xs)));
-      tile_add_at(add_word<1>(tile_lds, r3), round_to_fixed(mul_hi_f16(a.v[i].w, xs)));
-    }
+__device__ __forceinline__ void accumulate_pass_rows16(const Pass1& a, uint32_t cap_rows2, uint32_t tile_lds,
+                                                       uint32_t n_live, int lane) {
+  if (static_cast<uint32_t>(lane) < n_live) {
+    const float xs = a.xs;
+    const uint32_t r0 = min_u16x2(a.rr.x, cap_rows2) << 2, r1 = min_u16x2(a.rr.y, cap_rows2) << 2;
+    const uint32_t r2 = min_u16x2(a.rr.z, cap_rows2) << 2, r3 = min_u16x2(a.rr.w, cap_rows2) << 2;
+    tile_add_at(add_word<0>(tile_lds, r0), round_to_fixed(mul_lo_f16(a.v.x, xs)));
+    tile_add_at(add_word<1>(tile_lds, r0), round_to_fixed(mul_hi_f16(a.v.x, xs)));
+    tile_add_at(add_word<0>(tile_lds, r1), round_to_fixed(mul_lo_f16(a.v.y, xs)));
+    tile_add_at(add_word<1>(tile_lds, r1), round_to_fixed(mul_hi_f16(a.v.y, xs)));
+    tile_add_at(add_word<0>(tile_lds, r2), round_to_fixed(mul_lo_f16(a.v.z, xs)));
+    tile_add_at(add_word<1>(tile_lds, r2), round_to_fixed(mul_hi_f16(a.v.z, xs)));
+    tile_add_at(add_word<0>(tile_lds, r3), round_to_fixed(mul_lo_f16(a.v.w, xs)));
+    tile_add_at(add_word<1>(tile_lds, r3), round_to_fixed(mul_hi_f16(a.v.w, xs)));
   }
 }
 
@@ -613,7 +781,7 @@ __device__ __forceinline__ void fetch_pass_il(PassIl& a, const Streams& st, cons
     a.first = h == si.off;
     a.xs = si.xs;
     a.live = lv;
-    gl = lv ? si.gstart + (f - si.off) : 0u;
+    gl = lv ? si.base + f : 0u;
   }
   const auto v = __builtin_amdgcn_raw_buffer_load_b128(st.values, static_cast<int>(gl << 4), 0, kStreamPolicy);
   a.v = make_uint4(v[0], v[1], v[2], v[3]);
@@ -794,7 +962,7 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
     block_scan_select<WAVES>(keep ? 1u : 0u, cnt, keep ? __float_as_uint(fabsf(xv) * half_bits_to_float(cm[0])) : 0u,
                              en, eg, n_seg, n_grp, tmax, part);
     const int s = grid_scale(static_cast<float>(n_seg) * __uint_as_float(tmax), 30);
-    if (keep) seg[en] = SegInfo{g0, eg, cnt, ldexpf(xv, s)};
+    if (keep) seg[en] = SegInfo{g0 - eg, eg, cnt, ldexpf(xv, s)};
     scale = s;
   } else {
     // m <= kMaxCols consecutive columns per lane (loaded above), so one block
@@ -817,7 +985,7 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
     for (int j = 0; j < kMaxCols; ++j) {
       if ((keep_bits >> j) & 1u) {
         const uint32_t cnt = g[j + 1] - g[j];
-        seg[idx] = SegInfo{g[j], off, cnt, ldexpf(half_bits_to_float(xr[j]), s)};
+        seg[idx] = SegInfo{g[j] - off, off, cnt, ldexpf(half_bits_to_float(xr[j]), s)};
         ++idx;
         off += cnt;
       }
@@ -866,7 +1034,7 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
         int acc = 0;
         for (uint32_t j = lane; j - lane < before; j += kWave) {
           const uint32_t rw =
-              __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((s0.gstart + min(j, before - 1u)) << 2), 0, 0);
+              __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((s0.base + s0.off + min(j, before - 1u)) << 2), 0, 0);
           acc += j < before ? group_span4(rw) : 0;
         }
         carry = __builtin_amdgcn_readlane(wave_inclusive_scan(acc), kWave - 1);
@@ -895,10 +1063,12 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
     const uint32_t pe = cut_of<WAVES>(wvu + 1, n_grp);
     if (pb0 < pe) {
       SegInfo s0;
-      const int i_begin = holding_segment(seg, static_cast<int>(n_seg), pb0, lane, s0);
       const int i_end = static_cast<int>(n_seg);
       const Streams st = make_streams(p.values, p.runs, p.n_groups, VAR == kVarRows16 ? 16u : 4u);
       int* scr = scr_all + wv * kWave * scr_words_of(G, VAR);
+      uint32_t hw = 0u;     // head bits (one group per lane)
+      const int i_begin = G == 1 ? start_walk(seg, i_end, scr, pb0, pe, lane, s0, hw)
+                                 : holding_segment(seg, i_end, pb0, lane, s0);
       const int n_pass = static_cast<int>((pe - pb0 + P - 1) / P);
       // A range that starts inside a segment starts at the row reached by the
       // segment's earlier groups: their runs (up to 4 * 64 groups here, the
@@ -912,47 +1082,90 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
           // lanes past the earlier groups reread the last of them (their own
           // lines, not one line shared by every wavefront)
           const uint32_t j = min(static_cast<uint32_t>(q * kWave + lane), before - 1u);
-          rb[q] = __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((s0.gstart + j) << 2), 0, 0);
+          rb[q] = __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((s0.base + s0.off + j) << 2), 0, 0);
         }
       }
-      Pass<G> ring[DEPTH];
-      const uint32_t cap_rows2 = static_cast<uint32_t>(e.R + 7) * 0x00010001u;   // both halves: R + 7
-      uint32_t pf = pb0;    // flat start of the next pass to fetch
-      int icur = i_begin;   // segment holding group pf
-#pragma unroll
-      for (int d = 0; d < DEPTH; ++d) {
-        fetch_pass<G, VAR == kVarRows16>(ring[d], st, seg, scr, pf, icur, i_end, pe, lane);
-        icur = next_pass_segment<G>(ring[d], pf, i_end);
-        pf += P;
-      }
-      uint32_t pb = pb0;    // flat start of the pass being accumulated
-      int carry = 0;        // 4 * sum of (run + 1) over its first segment's earlier groups
-      if (before > 0u) {
+      const auto carry_in = [&]() -> int {   // 4 * sum of (run + 1) over its first segment's earlier groups
+        if (before == 0u) return 0;
         int acc = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) acc += static_cast<uint32_t>(q * kWave + lane) < before ? group_span4(rb[q]) : 0;
         for (uint32_t j = 4 * kWave + lane; j - lane < before; j += kWave) {   // segments longer than 256 groups
           const uint32_t rw =
-              __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((s0.gstart + min(j, before - 1u)) << 2), 0, 0);
+              __builtin_amdgcn_raw_buffer_load_b32(st.runs, static_cast<int>((s0.base + s0.off + min(j, before - 1u)) << 2), 0, 0);
           acc += j < before ? group_span4(rw) : 0;
         }
-        carry = __builtin_amdgcn_readlane(wave_inclusive_scan(acc), kWave - 1);
-      }
-      for (int done = 0; done < n_pass; done += DEPTH) {
+        return __builtin_amdgcn_readlane(wave_inclusive_scan(acc), kWave - 1);
+      };
+      uint32_t pf = pb0;    // flat start of the next pass to fetch
+      int icur = i_begin;   // segment holding group pf
+      uint32_t pb = pb0;    // flat start of the pass being accumulated
+      if constexpr (G == 1) {
+        const uint32_t cap_rows2 = static_cast<uint32_t>(e.R + 7) * 0x00010001u;   // both halves: R + 7
+        Pass1 ring[DEPTH];
+        int wi = 0;
+        const auto look = [&]() -> Look1 {
+          const Look1 k = look_pass1(seg, hw, wi, icur);
+          wi += 2;
+          return k;
+        };
+        const auto load = [&](Pass1& a, const Look1& k) {
+          load_pass1<VAR == kVarRows16>(a, k, st, pf, pe, lane);
+          pf += P;
+        };
+        Look1 first[DEPTH];
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-          if (pb < pe) {   // wavefront-uniform
-            if constexpr (VAR == kVarRows16) {
-              accumulate_pass_rows16<G>(ring[d], cap_rows2, tile_lds);
-            } else {
-              const int tail = accumulate_pass<G, VAR == kVarSwizzle>(ring[d], carry, base4_cap, tile_lds, scr, lane);
-              carry = ring[d].end63 > pb + P ? tail : 0;
-            }
+        for (int d = 0; d < DEPTH; ++d) first[d] = look();
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) load(ring[d], first[d]);
+        int carry = carry_in();
+        const auto accumulate = [&](const Pass1& a) {
+          if constexpr (VAR == kVarRows16) {
+            accumulate_pass_rows16(a, cap_rows2, tile_lds, pe - pb, lane);
+          } else {
+            const int tail = accumulate_pass1<VAR == kVarSwizzle>(a, carry, base4_cap, tile_lds, pe - pb, lane);
+            carry = a.cont ? tail : 0;
           }
           pb += P;
-          fetch_pass<G, VAR == kVarRows16>(ring[d], st, seg, scr, pf, icur, i_end, pe, lane);
+        };
+        // rounds of DEPTH passes that are followed by more, then the last ones
+        for (int left = n_pass; left > DEPTH; left -= DEPTH) {
+          if (wi == 2 * kHeadPasses) {   // the next kHeadPasses passes' heads
+            hw = head_bits(seg, i_end, scr, pf, icur + 1, true, min(pe - pf - 1u, 32u * kWave), lane);
+            wi = 0;
+          }
+#pragma unroll
+          for (int d = 0; d < DEPTH; ++d) {
+            const Look1 k = look();   // its LDS read passes while the slot's pass is decoded
+            accumulate(ring[d]);
+            load(ring[d], k);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+          if (pb < pe) accumulate(ring[d]);   // wavefront-uniform
+        }
+      } else {
+        Pass<G> ring[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+          fetch_pass<G>(ring[d], st, seg, scr, pf, icur, i_end, pe, lane);
           icur = next_pass_segment<G>(ring[d], pf, i_end);
           pf += P;
+        }
+        int carry = carry_in();
+        for (int done = 0; done < n_pass; done += DEPTH) {
+#pragma unroll
+          for (int d = 0; d < DEPTH; ++d) {
+            if (pb < pe) {   // wavefront-uniform
+              const int tail = accumulate_pass<G>(ring[d], carry, base4_cap, tile_lds, scr, lane);
+              carry = ring[d].end63 > pb + P ? tail : 0;
+            }
+            pb += P;
+            fetch_pass<G>(ring[d], st, seg, scr, pf, icur, i_end, pe, lane);
+            icur = next_pass_segment<G>(ring[d], pf, i_end);
+            pf += P;
+          }
         }
       }
     }
