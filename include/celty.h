@@ -170,7 +170,7 @@ celty_status celty_decode(const celty_rlc_csc* enc, uint16_t* W_out, uint8_t* ma
  *   idx    device, int32[K]: receives the active indices in ascending order;
  *          entries past |A| are not written.
  *   count  device, int32[1]: receives |A|.
- * One kernel launch of one workgroup.
+ * One kernel launch.
  * Errors: EINVAL (null pointers, K < 1 or K > (2^31 - 4) / 2, NaN tau,
  * misaligned x/idx/count), EHIP.
  */
