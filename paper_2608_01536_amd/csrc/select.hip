@@ -22,7 +22,7 @@ namespace {
 // between workgroups, at the price of reading x up to the range again (57 KB
 // at the widest activation of the LLM shapes, 16 bytes per lane and load, from
 // cache).  One workgroup alone takes 0.33 us per 2048 columns, almost all of
-// it the listing, and counting takes 0.02, so up to kSelBlocks workgroups
+// it the listing, and counting takes 0.08, so up to kSelBlocks workgroups
 // share the columns: us per call in a graph of 60, one workgroup -> now,
 // K = 28672 6.56 -> 3.38, 11008 3.86 -> 2.69, 4096 2.67 -> 2.44.
 //   * A range is taken in chunks of STEPS * 2048 columns; in a chunk, lane tid

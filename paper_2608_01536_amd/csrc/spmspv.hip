@@ -163,13 +163,14 @@ __device__ __forceinline__ uint32_t row_inclusive_max(uint32_t v) {
 // (WAVES <= 16).  Each wavefront's totals go to part[] (3*WAVES words, used
 // once per launch); after the barrier lane l < WAVES of every wavefront reads
 // wavefront l's totals and one row scan gives the offsets of all wavefronts.
-template <int WAVES>
+// ONE: a is 0 or 1, and its scan within a wavefront is a ballot.
+template <int WAVES, bool ONE>
 __device__ __forceinline__ void block_scan_select(uint32_t a, uint32_t b, uint32_t m, uint32_t& ea, uint32_t& eb,
                                                   uint32_t& ta, uint32_t& tb, uint32_t& tm, uint32_t* part) {
   static_assert(WAVES <= 16, "one DPP row holds the per-wavefront totals");
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
-  const uint32_t ia = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(a)));
+  const uint32_t ia = ONE ? lanes_below(__ballot(a != 0u)) + a : static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(a)));
   const uint32_t ib = static_cast<uint32_t>(wave_inclusive_scan(static_cast<int>(b)));
   const uint32_t im = wave_inclusive_max(m);
   if (lane == kWave - 1) {
@@ -858,7 +859,19 @@ struct KernelArgs {
   float tau;
   uint32_t n_groups;
   int M, K, R, Kc, KC;
+  uint32_t KC_inv;              // reciprocal_of(KC)
 };
+
+// floor(n / d) for d >= 1 and 0 <= n < 2^31 without a division (about 30
+// dependent instructions, ahead of a workgroup's first loads): with
+// inv = floor((2^32 - 1) / d), which is below 2^32 / d by at most 1,
+// n * inv / 2^32 is below n / d by less than 1/2, so its floor is at most one
+// too small.
+__host__ __device__ constexpr uint32_t reciprocal_of(int d) { return 0xFFFFFFFFu / static_cast<uint32_t>(d); }
+__device__ __forceinline__ int divide_by(int n, int d, uint32_t inv) {
+  const int q = static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(n)) * inv) >> 32);
+  return q + (n - q * d >= d ? 1 : 0);
+}
 
 // Up to kMaxBatch independent products in one launch: grid (max blocks, n),
 // product blockIdx.y owns workgroups blockIdx.x < blocks[blockIdx.y].  (The
@@ -881,6 +894,7 @@ struct Early {
   const unsigned short* x;
   const unsigned short* colmax;
   int K, Kc, KC;
+  uint32_t KC_inv;
   float tau;
   int R, M;
 };
@@ -901,7 +915,7 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
   uint32_t* part = reinterpret_cast<uint32_t*>(smem + lay.misc_off);   // 3*WAVES: the selection's scan
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
-  const int t = blk / e.KC, c = blk - t * e.KC;
+  const int t = divide_by(blk, e.KC, e.KC_inv), c = blk - t * e.KC;
 
   // The selection's loads go first: they need only the leading (preloaded)
   // arguments, so the workgroup's first memory round trip does not wait for
@@ -959,7 +973,7 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
     const bool keep = tid < kn && fabsf(xv) > e.tau && g1 > g0;
     const uint32_t cnt = keep ? g1 - g0 : 0u;
     uint32_t en, eg, tmax;
-    block_scan_select<WAVES>(keep ? 1u : 0u, cnt, keep ? __float_as_uint(fabsf(xv) * half_bits_to_float(cm[0])) : 0u,
+    block_scan_select<WAVES, true>(keep ? 1u : 0u, cnt, keep ? __float_as_uint(fabsf(xv) * half_bits_to_float(cm[0])) : 0u,
                              en, eg, n_seg, n_grp, tmax, part);
     const int s = grid_scale(static_cast<float>(n_seg) * __uint_as_float(tmax), 30);
     if (keep) seg[en] = SegInfo{g0 - eg, eg, cnt, ldexpf(xv, s)};
@@ -978,7 +992,7 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
       m_loc = max(m_loc, keep ? __float_as_uint(fabsf(xv) * half_bits_to_float(cm[j])) : 0u);
     }
     uint32_t en, eg, tmax;
-    block_scan_select<WAVES>(n_loc, g_loc, m_loc, en, eg, n_seg, n_grp, tmax, part);
+    block_scan_select<WAVES, false>(n_loc, g_loc, m_loc, en, eg, n_seg, n_grp, tmax, part);
     const int s = grid_scale(static_cast<float>(n_seg) * __uint_as_float(tmax), 30);
     uint32_t idx = en, off = eg;
 #pragma unroll
@@ -1276,8 +1290,8 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
 template <int WAVES, int G, int DEPTH, int VAR>
 __global__ __launch_bounds__(WAVES * kWave) void spmspv_kernel(const uint32_t* gptr, const unsigned short* x,
                                                                 const unsigned short* colmax, int K, int Kc, int KC,
-                                                                float tau, int R, int M, KernelArgs p) {
-  spmspv_block<WAVES, G, DEPTH, VAR>(Early{gptr, x, colmax, K, Kc, KC, tau, R, M}, p,
+                                                                uint32_t KC_inv, float tau, int R, int M, KernelArgs p) {
+  spmspv_block<WAVES, G, DEPTH, VAR>(Early{gptr, x, colmax, K, Kc, KC, KC_inv, tau, R, M}, p,
                                      static_cast<int>(blockIdx.x));
 }
 
@@ -1287,7 +1301,7 @@ __global__ __launch_bounds__(WAVES * kWave) void spmspv_batch_kernel(BatchArgs b
   const int pi = static_cast<int>(blockIdx.y);
   if (static_cast<int>(blockIdx.x) >= ba.blocks[pi]) return;   // past this product's grid
   const KernelArgs& p = ba.prod[pi];
-  spmspv_block<WAVES, G, DEPTH, kVarRlc>(Early{p.gptr, p.x, p.colmax, p.K, p.Kc, p.KC, p.tau, p.R, p.M},
+  spmspv_block<WAVES, G, DEPTH, kVarRlc>(Early{p.gptr, p.x, p.colmax, p.K, p.Kc, p.KC, p.KC_inv, p.tau, p.R, p.M},
                                          p, static_cast<int>(blockIdx.x));
 }
 
@@ -1435,8 +1449,8 @@ celty_status launch_shape(const Launch& ln, const BatchArgs& a, hipStream_t stre
       return CELTY_EHIP;
     const KernelArgs& q = a.prod[0];
     hipLaunchKernelGGL((spmspv_kernel<WAVES, G, DEPTH, VAR>), dim3(static_cast<unsigned>(ln.max_blocks)),
-                       dim3(WAVES * kWave), ln.lds, stream, q.gptr, q.x, q.colmax, q.K, q.Kc, q.KC, q.tau, q.R,
-                       q.M, q);
+                       dim3(WAVES * kWave), ln.lds, stream, q.gptr, q.x, q.colmax, q.K, q.Kc, q.KC,
+                       q.KC_inv, q.tau, q.R, q.M, q);
   } else if constexpr (VAR == kVarRlc) {
     if (ln.lds > 64 * 1024 && !allow_large_lds(&spmspv_batch_kernel<WAVES, G, DEPTH>, batch_attr))
       return CELTY_EHIP;
@@ -1507,6 +1521,7 @@ celty_status product_args(const celty_rlc_csc* W, const Plan& pl, const void* x,
   a.R = W->R;
   a.Kc = pl.Kc;
   a.KC = pl.KC;
+  a.KC_inv = reciprocal_of(pl.KC);
   return CELTY_OK;
 }
 
