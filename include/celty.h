@@ -180,9 +180,9 @@ celty_status celty_select(const void* x, int32_t K, float tau, int32_t* idx, int
 /* Launch shape of celty_spmspv_ex.  Zero fields mean "choose automatically":
  * 16 wavefronts per workgroup for R >= 1024, else 8; slices sized for about
  * 4096 / waves_per_block workgroups (16 wavefronts on each of 256 compute
- * units), never more, and widened to fill two 8-wavefront workgroups per
- * unit evenly when the rounded width would load the units unevenly and the
- * slices stay heavy enough; one group per lane.  The K columns are cut into
+ * units), never more; 8-wavefront workgroups are one per unit where a slice
+ * then has at most 512 columns, and fewer where a slice would be light for
+ * its merge; one group per lane.  The K columns are cut into
  * ceil(K / cols_per_block) slices, at most 63 (the merge counts 6-bit
  * arrivals in a 64-bit word).  A workgroup's lanes scan at most 8 columns
  * each: cols_per_block <= 512 * waves_per_block.

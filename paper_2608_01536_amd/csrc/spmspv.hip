@@ -1366,23 +1366,40 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     const int64_t kcs = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, (slots + W->T / 2) / W->T));
     int64_t kc = ((W->K + kcs - 1) / kcs + 63) / 64 * 64;
     const int64_t n_wg = W->T * ((W->K + kc - 1) / kc);
-    // Counts past the slots start a second round, and 8-wavefront counts
-    // between one and 0.9 x two per compute unit leave some units with two
-    // and the rest with one.  Then, with no rounding of the width: slices
-    // that would hold at least 80 KB of stored groups each at two workgroups
-    // per unit take the most slices that fit the slots (two per unit);
-    // lighter ones take one workgroup per unit, whose wider slices halve the
-    // merge tickets (16 bytes per row and slice), which outweigh the second
-    // workgroup's latency hiding on light slices.  Up to one workgroup per
-    // unit the count is kept.
+    // Counts past the slots start a second round.  8-wavefront counts past
+    // one per compute unit take one per unit where such a slice still gives
+    // every lane of the selection at most one column: the merge tickets (16
+    // bytes per row and slice) halve, and each wavefront's longer walk costs
+    // less than the second workgroup's prologue (us per product, graph of 60,
+    // two per unit -> one: 4096 x 11008 50/50 9.50 -> 9.12, 30/30 14.0 ->
+    // 13.5, 7168 x 7168 30/30 15.2 -> 14.6, 5003 x 3001 60/50 6.07 -> 5.61,
+    // 5120 x 12800 50/50 12.16 -> 12.26 the other way, the one such of 30).
+    // Wider slices, with several columns per lane, keep two per unit (5120 x
+    // 13824 60/60 10.3 against 11.6) in the most slices that fit the slots
+    // or, between one and 0.9 x two per unit, one per unit when the slices
+    // are light (under 80 KB of stored groups each at two per unit).  A
+    // matrix that stores all but 1/16 of its weights is not pruned; it keeps
+    // two per unit as well (5120 x 5120 ws 0 as 50: 11.53 against 11.46).
     const int64_t ks = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, slots / W->T));
+    const int64_t k1 = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, 256 / W->T));
+    const double stored = 20.0 * static_cast<double>(W->n_groups);   // bytes of groups
+    const bool dense = stored >= 15.0 / 16.0 * 2.5 * static_cast<double>(W->M) * static_cast<double>(W->K);
     const bool uneven = pl.waves == 8 && n_wg > 256 && 10 * n_wg < 9 * slots;
-    const double stored_per_wg = 20.0 * static_cast<double>(W->n_groups) / static_cast<double>(W->T * ks);
-    if (n_wg > slots || (uneven && stored_per_wg >= 80.0 * 1024.0)) {
+    if (pl.waves == 8 && n_wg > 256 && !dense && (W->K + k1 - 1) / k1 <= kWave * pl.waves) {
+      kc = (W->K + k1 - 1) / k1;
+    } else if (n_wg > slots || (uneven && stored >= 80.0 * 1024.0 * static_cast<double>(W->T * ks))) {
       kc = (W->K + ks - 1) / ks;
     } else if (uneven) {
-      const int64_t k1 = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, 256 / W->T));
       kc = (W->K + k1 - 1) / k1;
+    } else if (pl.waves == 8 && n_wg > 128 && stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
+      // up to one workgroup per unit the count is kept, unless a workgroup
+      // would hold less than 112 bytes of stored groups for each ticket of
+      // its merge: then fewer, down to 128 (4096 x 4096 ws 70 as 70 5.04 with
+      // 256, 4.91 with 224; ws 80 as 80 4.96, 4.59 with 160; ws 50, above the
+      // line, 6.06 and 6.13; 3000 x 3000 ws 70 as 70, below it, 4.29 and 4.30)
+      const int64_t n = std::max<int64_t>(128, static_cast<int64_t>(stored / (112.0 * static_cast<double>(W->R))));
+      const int64_t k = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, n / W->T));
+      kc = (W->K + k - 1) / k;
     }
     kc = std::min<int64_t>(kc, std::min(4096, kMaxCols * kWave * pl.waves));
     Kc = static_cast<int>(kc);

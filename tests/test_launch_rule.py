@@ -1,0 +1,33 @@
+"""The automatic launch shape's rule for 8-wavefront workgroups (host only):
+one workgroup per compute unit where a slice then has at most one column per
+lane, two per unit where it would have more or where nothing is pruned, and
+fewer than one where a workgroup holds little for its merge."""
+import ctypes
+
+import pytest
+
+import paper_2608_01536_amd as celty
+
+FAKE = 0x10000
+
+
+@pytest.mark.parametrize("M,K,density,cols,blocks", [
+    (4096, 11008, 0.5, 344, 256),     # one per unit
+    (5120, 12800, 0.5, 512, 250),     # exactly one column per lane
+    (5120, 12801, 0.5, 256, 510),     # more: two per unit
+    (5120, 13824, 0.5, 272, 510),
+    (7168, 7168, 0.5, 399, 252),
+    (7168, 7168, 1.0, 200, 504),      # nothing pruned
+    (7168, 7168, 0.93, 399, 252),     # just under 15/16
+    (4096, 4096, 0.5, 128, 256),      # heavy enough for its merge
+    (4096, 4096, 0.3, 152, 216),      # light: 112 bytes per ticket
+    (4096, 4096, 0.1, 256, 128),      # never below 128
+    (512, 2048, 0.1, 64, 64),         # already below
+    (8192, 8192, 0.5, 256, 256),      # 16 wavefronts: as before
+])
+def test_automatic_slices(M, K, density, cols, blocks):
+    R = celty.default_tile_rows(M, K)
+    d = celty.celty_rlc_csc(2, M, K, R, -(-M // R), 4, int(M * K * density) // 8, 0, 0, 0, 1.0, 0, FAKE, FAKE, FAKE, FAKE)
+    out, n = celty.celty_launch(), ctypes.c_int64()
+    assert celty._plan(ctypes.byref(d), None, ctypes.byref(out), ctypes.byref(n), None) == celty.CELTY_OK
+    assert (out.cols_per_block, n.value) == (cols, blocks)
