@@ -873,13 +873,20 @@ __device__ __forceinline__ int divide_by(int n, int d, uint32_t inv) {
   return q + (n - q * d >= d ? 1 : 0);
 }
 
-// Up to kMaxBatch independent products in one launch: grid (max blocks, n),
-// product blockIdx.y owns workgroups blockIdx.x < blocks[blockIdx.y].  (The
-// product is found from the block index alone, so its arguments arrive with
-// one scalar load latency, as for a single product.)
+// Up to kMaxBatch independent products in one launch: their workgroups follow
+// one another in one row, product i's from start[i].  A workgroup finds its
+// product from the starts, which are leading (preloaded) kernel arguments, and
+// then reads the product's arguments: one scalar load latency more than for a
+// single product.
+//
+// (A row per product, with a return for the workgroups past a shorter
+// product's, launched up to twice the workgroups and read a count before the
+// arguments.  us per launch in a graph of 60, a row per product -> one row:
+// 2 x 5632 x 2048 6.50 -> 6.22, 3 x 4096 x 4096 50/50 11.30 -> 11.07,
+// 2 x 11008 x 4096 15.54 -> 15.42.)
 constexpr int kMaxBatch = 8;
+constexpr int kBatchRow = 1 << 21;   // workgroups along x: their lanes are counted in 32 bits
 struct BatchArgs {
-  int blocks[kMaxBatch];
   KernelArgs prod[kMaxBatch];
 };
 
@@ -1295,14 +1302,23 @@ __global__ __launch_bounds__(WAVES * kWave) void spmspv_kernel(const uint32_t* g
                                      static_cast<int>(blockIdx.x));
 }
 
-// (several products: the RLC layout and the plain tile only)
+// (several products: the RLC layout and the plain tile only; s1 .. s7: first
+// workgroups of products 1 .. 7, INT32_MAX for those not there)
 template <int WAVES, int G, int DEPTH>
-__global__ __launch_bounds__(WAVES * kWave) void spmspv_batch_kernel(BatchArgs ba) {
-  const int pi = static_cast<int>(blockIdx.y);
-  if (static_cast<int>(blockIdx.x) >= ba.blocks[pi]) return;   // past this product's grid
+__global__ __launch_bounds__(WAVES * kWave) void spmspv_batch_kernel(int s1, int s2, int s3, int s4, int s5, int s6,
+                                                                      int s7, int blocks, BatchArgs ba) {
+  const int blk = static_cast<int>(blockIdx.y) * kBatchRow + static_cast<int>(blockIdx.x);
+  if (blk >= blocks) return;   // past the last row's end
+  const int starts[kMaxBatch] = {0, s1, s2, s3, s4, s5, s6, s7};
+  int pi = 0, start = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxBatch; ++i) {
+    pi = blk >= starts[i] ? i : pi;
+    start = blk >= starts[i] ? starts[i] : start;
+  }
   const KernelArgs& p = ba.prod[pi];
-  spmspv_block<WAVES, G, DEPTH, kVarRlc>(Early{p.gptr, p.x, p.colmax, p.K, p.Kc, p.KC, p.KC_inv, p.tau, p.R, p.M},
-                                         p, static_cast<int>(blockIdx.x));
+  spmspv_block<WAVES, G, DEPTH, kVarRlc>(Early{p.gptr, p.x, p.colmax, p.K, p.Kc, p.KC, p.KC_inv, p.tau, p.R, p.M}, p,
+                                         blk - start);
 }
 
 // Zero-fills n bytes at p: the bytes before the first 8-byte boundary, then
@@ -1434,11 +1450,12 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
   return CELTY_OK;
 }
 
-// The launch: products, the largest per-product grid and LDS footprint.
+// The launch: products, their workgroups and the largest LDS footprint.
 struct Launch {
   int waves = 8, groups = 1, n = 0, var = kVarRlc;
   bool shallow = false;   // one group per lane with a ring of two passes instead of three
-  int64_t max_blocks = 0;
+  int64_t blocks = 0;     // of all products
+  int start[kMaxBatch];   // first workgroup of each product (INT32_MAX past the last)
   size_t lds = 0;
 };
 
@@ -1465,15 +1482,17 @@ celty_status launch_shape(const Launch& ln, const BatchArgs& a, hipStream_t stre
     if (ln.lds > 64 * 1024 && !allow_large_lds(&spmspv_kernel<WAVES, G, DEPTH, VAR>, single_attr))
       return CELTY_EHIP;
     const KernelArgs& q = a.prod[0];
-    hipLaunchKernelGGL((spmspv_kernel<WAVES, G, DEPTH, VAR>), dim3(static_cast<unsigned>(ln.max_blocks)),
+    hipLaunchKernelGGL((spmspv_kernel<WAVES, G, DEPTH, VAR>), dim3(static_cast<unsigned>(ln.blocks)),
                        dim3(WAVES * kWave), ln.lds, stream, q.gptr, q.x, q.colmax, q.K, q.Kc, q.KC,
                        q.KC_inv, q.tau, q.R, q.M, q);
   } else if constexpr (VAR == kVarRlc) {
     if (ln.lds > 64 * 1024 && !allow_large_lds(&spmspv_batch_kernel<WAVES, G, DEPTH>, batch_attr))
       return CELTY_EHIP;
     hipLaunchKernelGGL((spmspv_batch_kernel<WAVES, G, DEPTH>),
-                       dim3(static_cast<unsigned>(ln.max_blocks), static_cast<unsigned>(ln.n)),
-                       dim3(WAVES * kWave), ln.lds, stream, a);
+                       dim3(static_cast<unsigned>(std::min<int64_t>(ln.blocks, kBatchRow)),
+                            static_cast<unsigned>((ln.blocks + kBatchRow - 1) / kBatchRow)),
+                       dim3(WAVES * kWave), ln.lds, stream, ln.start[1], ln.start[2], ln.start[3], ln.start[4],
+                       ln.start[5], ln.start[6], ln.start[7], static_cast<int>(ln.blocks), a);
   } else {
     return CELTY_EINVAL;   // rejected by celty_spmspv_batch before this point
   }
@@ -1666,7 +1685,7 @@ extern "C" celty_status celty_spmspv_batch(int32_t n, const celty_rlc_csc* const
 
   BatchArgs ba{};
   ln.n = n;
-  int64_t total_blocks = 0;
+  std::fill(ln.start, ln.start + kMaxBatch, INT32_MAX);
   double stored_groups = 0.0;
   size_t ws_off = 0;
   for (int i = 0; i < n; ++i) {
@@ -1678,10 +1697,10 @@ extern "C" celty_status celty_spmspv_batch(int32_t n, const celty_rlc_csc* const
     void* ws_i = static_cast<unsigned char*>(workspace) + ws_off;
     if (celty_status st = product_args(W[i], pl, x[i], tau[i], y[i], ws_i, ba.prod[i])) return st;
     ws_off += celty_spmspv_workspace_bytes(W[i]->M, W[i]->K, W[i]->R);
-    ba.blocks[i] = static_cast<int>(pl.blocks);   // make_plan keeps it below 2^31
-    ln.max_blocks = std::max(ln.max_blocks, pl.blocks);
+    if (ln.blocks > INT32_MAX - kBatchRow - pl.blocks) return CELTY_EINVAL;   // workgroup numbers are ints
+    ln.start[i] = static_cast<int>(ln.blocks);
+    ln.blocks += pl.blocks;
     ln.lds = std::max(ln.lds, pl.lds);
-    total_blocks += pl.blocks;
     stored_groups += static_cast<double>(W[i]->n_groups);
   }
   // every y is written while the other products read their x; none may
@@ -1702,8 +1721,8 @@ extern "C" celty_status celty_spmspv_batch(int32_t n, const celty_rlc_csc* const
   // 16-wavefront workgroups, keep three.  The pass count is estimated with
   // half of the stored groups active (the activation is not known here).
   const double passes =
-      total_blocks > 0 ? 0.5 * stored_groups / (static_cast<double>(total_blocks) * ln.waves * kWave) : 0.0;
-  ln.shallow = ln.groups == 1 && ln.waves == 8 && total_blocks > 256 && passes >= 4.0 && passes <= 16.0;
+      ln.blocks > 0 ? 0.5 * stored_groups / (static_cast<double>(ln.blocks) * ln.waves * kWave) : 0.0;
+  ln.shallow = ln.groups == 1 && ln.waves == 8 && ln.blocks > 256 && passes >= 4.0 && passes <= 16.0;
   return launch(ln, ba, static_cast<hipStream_t>(stream));
 }
 
