@@ -6,6 +6,12 @@
 // contiguous in the tile-major layout, so items never write the same bytes
 // and the output does not depend on the thread count.
 //
+// A random mask makes a branch per weight mispredict every other time, which
+// was most of the time: the counting is branch-free in 16-bit vector lanes,
+// and the fill takes each row's stored columns from a list made without
+// branches.  Plan and encode of 4096 x 4096 at 50 % weight sparsity, 8 cores:
+// 66 -> 13 ms (the plan alone 20.8 -> 1.6).
+//
 // Three layouts of the rows: 4-bit runs (the paper's); 16-bit row offsets
 // within the tile (no padding entries, a decode-free form); and the RLC
 // entries of each segment in lane-interleaved order within chunks of up to
@@ -25,14 +31,11 @@ namespace {
 
 constexpr int kCap = (1 << CELTY_RUN_BITS) - 1;   // largest run a padding entry carries
 constexpr int kColBlock = 512;                      // columns per work item
+// Columns filled at a time: their open cache lines (one of values and one of
+// runs each, 16 KB) stay in the first-level cache while the rows go by.
+constexpr int kFillBlock = 128;
 constexpr int kChunk = 64;                          // groups per interleave chunk (a wavefront's lanes)
 constexpr int32_t kMaxRows16 = 16376;               // tile rows of ROWS16: 4 * (R + 7) fits in 16 bits
-
-inline bool stored(const uint16_t* W, int64_t ldw, const uint8_t* mask, int64_t ldm, int64_t r,
-                   int64_t k) {
-  if ((W[r * ldw + k] & 0x7FFFu) == 0) return false;   // +0 / -0 are never stored
-  return mask == nullptr || mask[r * ldm + k] != 0;
-}
 
 // Exact value of an fp16 bit pattern (finite or not).
 float half_bits_to_float(uint16_t h) {
@@ -101,31 +104,82 @@ bool parallel_items(size_t n_items, int32_t n_threads, Fn fn) {
   return !failed.load();
 }
 
+// One row of a count: s = -1 where the entry is stored, else 0 (+0 and -0 are
+// never stored).  A random mask makes a branch per entry mispredict every
+// other time, so the state is updated without branches, in lanes of type I.
+template <class I, bool MASK, bool BRIDGE>
+void count_row(const uint16_t* w, const uint8_t* m, int32_t nk, I rel, I* __restrict last, I* __restrict cnt,
+               I* __restrict pad, uint16_t* __restrict cmax) {
+  for (int32_t j = 0; j < nk; ++j) {
+    const uint16_t mag = uint16_t(w[j] & 0x7FFFu);
+    const I s = I(-I((mag != 0) & (!MASK || m[j] != 0)));
+    const I np = BRIDGE ? I(I(rel - last[j] - 1) >> CELTY_RUN_BITS) : I(0);   // padding entries before it (gap / 16)
+    cnt[j] = I(cnt[j] + (s & I(np + 1)));
+    pad[j] = I(pad[j] + (s & np));
+    last[j] = I((s & rel) | (~s & last[j]));
+    const uint16_t v = uint16_t(uint16_t(s) & mag);   // magnitude bits order like the values
+    cmax[j] = cmax[j] > v ? cmax[j] : v;
+  }
+}
+
 // Counts entries per segment of one item; writes groups per segment into
-// seg_groups (indexed s - (t*K + k0)) when non-null and adds the totals.
-void count_item(const uint16_t* W, int64_t ldw, const uint8_t* mask, int64_t ldm, int32_t M,
-                int32_t R, bool bridge, const Item& it, std::vector<int32_t>& last, std::vector<int64_t>& cnt,
-                int64_t& nnz, int64_t& pad, int64_t& groups, uint32_t* seg_groups) {
+// seg_groups and the largest |value| bits per segment into seg_max (indexed
+// s - (t*K + k0)) when non-null, and gives the totals.
+template <class I>
+void count_item_as(const uint16_t* W, int64_t ldw, const uint8_t* mask, int64_t ldm, int32_t M, int32_t R, bool bridge,
+                   const Item& it, int64_t& nnz, int64_t& pad, int64_t& groups, uint32_t* seg_groups,
+                   uint16_t* seg_max) {
+  static_assert(CELTY_GROUP == 8, "groups by shifts");
+  I last[kColBlock], cnt[kColBlock], pads[kColBlock];
+  uint16_t cmax[kColBlock];
   const int32_t nk = it.k1 - it.k0;
   const int64_t r0 = int64_t(it.t) * R, r1 = std::min<int64_t>(M, r0 + R);
-  std::fill(last.begin(), last.begin() + nk, -1);
-  std::fill(cnt.begin(), cnt.begin() + nk, 0);
+  std::fill(last, last + nk, I(-1));
+  std::fill(cnt, cnt + nk, I(0));
+  std::fill(pads, pads + nk, I(0));
+  std::fill(cmax, cmax + nk, uint16_t(0));
   for (int64_t r = r0; r < r1; ++r) {
-    const int32_t rel = int32_t(r - r0);
-    for (int32_t j = 0; j < nk; ++j) {
-      if (!stored(W, ldw, mask, ldm, r, it.k0 + j)) continue;
-      const int32_t np = bridge ? (rel - last[j] - 1) / (kCap + 1) : 0;   // padding entries before it
-      cnt[j] += np + 1;
-      pad += np;
-      ++nnz;
-      last[j] = rel;
-    }
+    const uint16_t* w = W + r * ldw + it.k0;
+    const uint8_t* m = mask ? mask + r * ldm + it.k0 : nullptr;
+    const I rel = I(r - r0);
+    if (mask)
+      bridge ? count_row<I, true, true>(w, m, nk, rel, last, cnt, pads, cmax)
+             : count_row<I, true, false>(w, m, nk, rel, last, cnt, pads, cmax);
+    else
+      bridge ? count_row<I, false, true>(w, m, nk, rel, last, cnt, pads, cmax)
+             : count_row<I, false, false>(w, m, nk, rel, last, cnt, pads, cmax);
   }
+  nnz = pad = groups = 0;
   for (int32_t j = 0; j < nk; ++j) {
-    const int64_t g = (cnt[j] + CELTY_GROUP - 1) / CELTY_GROUP;
+    const int64_t g = (int64_t(cnt[j]) + CELTY_GROUP - 1) / CELTY_GROUP;
     groups += g;
+    pad += pads[j];
+    nnz += int64_t(cnt[j]) - pads[j];
     if (seg_groups) seg_groups[j] = uint32_t(g);
+    if (seg_max) seg_max[j] = cmax[j];
   }
+}
+
+// A segment has at most as many entries as its tile has rows (each covers at
+// least one), so 16-bit lanes hold tiles of up to 32767 rows.
+void count_item(const uint16_t* W, int64_t ldw, const uint8_t* mask, int64_t ldm, int32_t M, int32_t R, bool bridge,
+                const Item& it, int64_t& nnz, int64_t& pad, int64_t& groups, uint32_t* seg_groups,
+                uint16_t* seg_max) {
+  if (std::min(M, R) <= INT16_MAX)
+    count_item_as<int16_t>(W, ldw, mask, ldm, M, R, bridge, it, nnz, pad, groups, seg_groups, seg_max);
+  else
+    count_item_as<int32_t>(W, ldw, mask, ldm, M, R, bridge, it, nnz, pad, groups, seg_groups, seg_max);
+}
+
+// The columns of one row that are stored, ascending, into list; returns how
+// many.  Without a branch per entry, as above.
+int32_t stored_columns(const uint16_t* w, const uint8_t* m, int32_t nk, uint16_t* list) {
+  int32_t n = 0;
+  for (int32_t j = 0; j < nk; ++j) {
+    list[n] = uint16_t(j);
+    n += int32_t((w[j] & 0x7FFFu) != 0) & int32_t(m == nullptr || m[j] != 0);
+  }
+  return n;
 }
 
 celty_status check_common(const uint16_t* W, int64_t ldw, const uint8_t* mask, int64_t ldm,
@@ -173,10 +227,8 @@ extern "C" celty_status celty_encode_plan(const uint16_t* W, int64_t ldw, const 
     const std::vector<Item> items = make_items(T, K);
     std::vector<int64_t> nnz(items.size()), pad(items.size()), grp(items.size());
     bool ok = parallel_items(items.size(), 0, [&](size_t i) {
-      std::vector<int32_t> last(kColBlock);
-      std::vector<int64_t> cnt(kColBlock);
       int64_t a = 0, b = 0, c = 0;
-      count_item(W, ldw, mask, ldm, M, R, layout != CELTY_LAYOUT_ROWS16, items[i], last, cnt, a, b, c, nullptr);
+      count_item(W, ldw, mask, ldm, M, R, layout != CELTY_LAYOUT_ROWS16, items[i], a, b, c, nullptr, nullptr);
       nnz[i] = a;
       pad[i] = b;
       grp[i] = c;
@@ -224,10 +276,9 @@ extern "C" celty_status celty_encode(const uint16_t* W, int64_t ldw, const uint8
     // pass 1: groups per segment, written into gptr[s] (then scanned in place)
     bool ok = parallel_items(items.size(), n_threads, [&](size_t i) {
       const Item& it = items[i];
-      std::vector<int32_t> last(kColBlock);
-      std::vector<int64_t> cnt(kColBlock);
+      const int64_t sbase = int64_t(it.t) * K + it.k0;
       int64_t a = 0, b = 0, c = 0;
-      count_item(W, ldw, mask, ldm, M, R, !rows16, it, last, cnt, a, b, c, gptr + int64_t(it.t) * K + it.k0);
+      count_item(W, ldw, mask, ldm, M, R, !rows16, it, a, b, c, gptr + sbase, tile_colmax.data() + sbase);
       nnz[i] = a;
       pad[i] = b;
     });
@@ -247,47 +298,61 @@ extern "C" celty_status celty_encode(const uint16_t* W, int64_t ldw, const uint8
       const Item& it = items[i];
       const int32_t nk = it.k1 - it.k0;
       const int64_t sbase = int64_t(it.t) * K + it.k0;
-      const int64_t g0 = gptr[sbase], g1 = gptr[sbase + nk];
-      const int64_t run_words = rows16 ? 4 : 1;   // words of row information per group
-      std::memset(values + g0 * CELTY_GROUP, 0, size_t(g1 - g0) * CELTY_GROUP * sizeof(uint16_t));
-      std::memset(runs + g0 * run_words, 0, size_t(g1 - g0) * run_words * sizeof(uint32_t));
       uint16_t* rows = reinterpret_cast<uint16_t*>(runs);   // ROWS16: entry e's offset at rows[e]
-      std::vector<int32_t> last(nk, -1);
-      std::vector<int64_t> pos(nk);   // next entry index (absolute) of each segment
-      for (int32_t j = 0; j < nk; ++j) pos[j] = int64_t(gptr[sbase + j]) * CELTY_GROUP;
-      auto emit = [&](int32_t j, uint16_t v, uint32_t run) {
-        const int64_t e = pos[j]++;
-        values[e] = v;
-        runs[e / CELTY_GROUP] |= run << (4 * (e % CELTY_GROUP));
-      };
       const int64_t r0 = int64_t(it.t) * R, r1 = std::min<int64_t>(M, r0 + R);
-      for (int64_t r = r0; r < r1; ++r) {
-        const int32_t rel = int32_t(r - r0);
-        for (int32_t j = 0; j < nk; ++j) {
-          if (!stored(W, ldw, mask, ldm, r, it.k0 + j)) continue;
-          const uint16_t v = W[r * ldw + it.k0 + j];
-          if (rows16) {
-            const int64_t e = pos[j]++;
-            values[e] = v;
-            rows[e] = uint16_t(rel);
-          } else {
-            int32_t gap = rel - last[j] - 1;
-            while (gap > kCap) {          // padding first, carrying the largest run
-              emit(j, 0, uint32_t(kCap));
-              gap -= kCap + 1;
-            }
-            emit(j, v, uint32_t(gap));
-          }
-          uint16_t& cm = tile_colmax[size_t(sbase + j)];
-          cm = std::max<uint16_t>(cm, uint16_t(v & 0x7FFFu));   // magnitude bits order like the values
-          last[j] = rel;
+      uint16_t list[kFillBlock];
+      int32_t last[kFillBlock];
+      int64_t pos[kFillBlock];    // next entry index (absolute) of each segment
+      uint32_t word[kFillBlock];  // the runs of its open group
+      for (int32_t j0 = 0; j0 < nk; j0 += kFillBlock) {
+        const int32_t nf = std::min(kFillBlock, nk - j0);
+        for (int32_t j = 0; j < nf; ++j) {
+          last[j] = -1;
+          pos[j] = int64_t(gptr[sbase + j0 + j]) * CELTY_GROUP;
+          word[j] = 0;
         }
-      }
-      // alignment entries: (0, 0) from the memset for runs; for row offsets,
-      // value 0 at the segment's last stored row
-      if (rows16) {
-        for (int32_t j = 0; j < nk; ++j)
-          for (int64_t e = pos[j]; e < int64_t(gptr[sbase + j + 1]) * CELTY_GROUP; ++e) rows[e] = uint16_t(last[j]);
+        // every entry stores its group's runs so far (a full group's last
+        // store is its word), so nothing is cleared beforehand
+        auto emit = [&](int32_t j, uint16_t v, uint32_t run) {
+          const int64_t e = pos[j]++;
+          const uint32_t slot = uint32_t(e) % CELTY_GROUP;
+          const uint32_t w = word[j] | (run << (4 * slot));
+          values[e] = v;
+          runs[e / CELTY_GROUP] = w;
+          word[j] = slot == CELTY_GROUP - 1 ? 0u : w;
+        };
+        for (int64_t r = r0; r < r1; ++r) {
+          const int32_t rel = int32_t(r - r0);
+          const uint16_t* w = W + r * ldw + it.k0 + j0;
+          const int32_t n = stored_columns(w, mask ? mask + r * ldm + it.k0 + j0 : nullptr, nf, list);
+          if (rows16) {
+            for (int32_t i2 = 0; i2 < n; ++i2) {
+              const int32_t j = list[i2];
+              const int64_t e = pos[j]++;
+              values[e] = w[j];
+              rows[e] = uint16_t(rel);
+              last[j] = rel;
+            }
+          } else {
+            for (int32_t i2 = 0; i2 < n; ++i2) {
+              const int32_t j = list[i2];
+              int32_t gap = rel - last[j] - 1;
+              while (gap > kCap) {          // padding first, carrying the largest run
+                emit(j, 0, uint32_t(kCap));
+                gap -= kCap + 1;
+              }
+              emit(j, w[j], uint32_t(gap));
+              last[j] = rel;
+            }
+          }
+        }
+        // alignment entries: (0, 0), their runs left clear by emit; for row
+        // offsets, value 0 at the segment's last stored row
+        for (int32_t j = 0; j < nf; ++j)
+          for (int64_t e = pos[j]; e < int64_t(gptr[sbase + j0 + j + 1]) * CELTY_GROUP; ++e) {
+            values[e] = 0;
+            if (rows16) rows[e] = uint16_t(last[j]);
+          }
       }
       if (layout == CELTY_LAYOUT_INTERLEAVED) {
         std::vector<uint16_t> tv(kChunk * CELTY_GROUP);
