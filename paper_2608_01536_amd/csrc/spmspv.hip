@@ -433,9 +433,9 @@ __device__ __forceinline__ uint32_t min_u16x2(uint32_t w, uint32_t c) {
 
 // Decodes one pass and adds its products into the fixed-point tile at LDS
 // byte address tile_lds.  Row arithmetic is done on byte offsets, 4 * row: a
-// group's runs r_0..r_7 put entry j at 4 * (base + sum_{i<=j} (r_i + 1)), so
+// group's runs r_0..r_7 put entry j at 4 * (base + sum_{i<=j} r_i + j), so
 // one running address advances by the byte 4 * r_j per entry and the
-// constant 4 * (j + 1) is an immediate.  Returns the
+// constant 4 * j is an immediate.  Returns the
 // segment-relative sum of 4 * (run + 1) through lane 63's last group (the
 // carry when that segment goes on into the next pass), wavefront-uniform.
 template <int G>
