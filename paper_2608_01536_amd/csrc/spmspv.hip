@@ -1383,7 +1383,8 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     int64_t kc = ((W->K + kcs - 1) / kcs + 63) / 64 * 64;
     const int64_t n_wg = W->T * ((W->K + kc - 1) / kc);
     // Counts past the slots start a second round.  8-wavefront counts past
-    // one per compute unit take one per unit where such a slice still gives
+    // one per compute unit (on the tiles that take 8 by themselves, under 1024
+    // rows) take one per unit where such a slice still gives
     // every lane of the selection at most one column: the merge tickets (16
     // bytes per row and slice) halve, and each wavefront's longer walk costs
     // less than the second workgroup's prologue (us per product, graph of 60,
@@ -1401,13 +1402,14 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     const double stored = 20.0 * static_cast<double>(W->n_groups);   // bytes of groups
     const bool dense = stored >= 15.0 / 16.0 * 2.5 * static_cast<double>(W->M) * static_cast<double>(W->K);
     const bool uneven = pl.waves == 8 && n_wg > 256 && 10 * n_wg < 9 * slots;
-    if (pl.waves == 8 && n_wg > 256 && !dense && (W->K + k1 - 1) / k1 <= kWave * pl.waves) {
+    const bool low = pl.waves == 8 && W->R < 1024;
+    if (low && n_wg > 256 && !dense && (W->K + k1 - 1) / k1 <= kWave * pl.waves) {
       kc = (W->K + k1 - 1) / k1;
     } else if (n_wg > slots || (uneven && stored >= 80.0 * 1024.0 * static_cast<double>(W->T * ks))) {
       kc = (W->K + ks - 1) / ks;
     } else if (uneven) {
       kc = (W->K + k1 - 1) / k1;
-    } else if (pl.waves == 8 && n_wg > 128 && stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
+    } else if (low && n_wg > 128 && stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
       // up to one workgroup per unit the count is kept, unless a workgroup
       // would hold less than 112 bytes of stored groups for each ticket of
       // its merge: then fewer, down to 128 (4096 x 4096 ws 70 as 70 5.04 with

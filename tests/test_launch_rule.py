@@ -31,3 +31,14 @@ def test_automatic_slices(M, K, density, cols, blocks):
     out, n = celty.celty_launch(), ctypes.c_int64()
     assert celty._plan(ctypes.byref(d), None, ctypes.byref(out), ctypes.byref(n), None) == celty.CELTY_OK
     assert (out.cols_per_block, n.value) == (cols, blocks)
+
+
+def test_tall_tiles_keep_their_slices():
+    # 8 wavefronts asked for on a tall tile: wider slices would not leave the
+    # tile room in LDS
+    M, K, R = 200000, 15000, 39000
+    d = celty.celty_rlc_csc(2, M, K, R, -(-M // R), 4, 3 * 10 ** 6, 0, 0, 0, 1.0, 0, FAKE, FAKE, FAKE, FAKE)
+    out, n = celty.celty_launch(), ctypes.c_int64()
+    L = celty.celty_launch(0, 8, 0, 0)
+    assert celty._plan(ctypes.byref(d), ctypes.byref(L), ctypes.byref(out), ctypes.byref(n), None) == celty.CELTY_OK
+    assert (out.cols_per_block, n.value) == (239, 378)
