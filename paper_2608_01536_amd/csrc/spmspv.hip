@@ -1409,14 +1409,26 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
       kc = (W->K + ks - 1) / ks;
     } else if (uneven) {
       kc = (W->K + k1 - 1) / k1;
-    } else if (low && n_wg > 128 && stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
+    } else if (low && n_wg > 128 && n_wg <= 256 && kc <= kWave * pl.waves &&
+               stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
       // up to one workgroup per unit the count is kept, unless a workgroup
       // would hold less than 112 bytes of stored groups for each ticket of
-      // its merge: then fewer, down to 128 (4096 x 4096 ws 70 as 70 5.04 with
-      // 256, 4.91 with 224; ws 80 as 80 4.96, 4.59 with 160; ws 50, above the
-      // line, 6.06 and 6.13; 3000 x 3000 ws 70 as 70, below it, 4.29 and 4.30)
+      // its merge: then fewer, down to the whole slices of 128, as long as
+      // every lane of the selection keeps to one column.  Kept count -> this
+      // one, us at as 0, 50, 90: 4096 x 4096 ws 70 6.44 -> 6.39, 5.57 -> 5.44,
+      // 4.86 -> 4.70; 2048 x 2048 ws 80 4.33 -> 4.31, 4.32 -> 4.01, 4.28 ->
+      // 3.89; 801 x 3582 ws 50 5.31 -> 5.37, 4.81 -> 4.52, 4.72 -> 4.19; where
+      // it loses, 4088 x 841 ws 60 4.29 -> 4.57, 4.09 -> 4.22, 3.94 -> 3.84.
+      // Beyond either limit it loses more: 5838 x 15932 ws 95 504 -> 372
+      // workgroups (two columns per lane) 6.52 -> 8.74, 6732 x 10452 ws 90 462
+      // -> 392 6.41 -> 7.08, 624 x 23864 ws 95 to 555 columns 5.26 -> 6.29.
+      // The matrices of the counts above one per unit that went to one of
+      // their own (the first branch) are not cut further: 5003 x 3001 ws 80 as
+      // 50 250 -> 180 -> 130 workgroups 5.03, 4.96, 5.33, 6000 x 4000 ws 80
+      // 252 -> 180 5.07 -> 5.38.
       const int64_t n = std::max<int64_t>(128, static_cast<int64_t>(stored / (112.0 * static_cast<double>(W->R))));
-      const int64_t k = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, n / W->T));
+      const int64_t lanes = static_cast<int64_t>(kWave) * pl.waves;
+      const int64_t k = std::max<int64_t>({1, n / W->T, (W->K + lanes - 1) / lanes});
       kc = (W->K + k - 1) / k;
     }
     kc = std::min<int64_t>(kc, std::min(4096, kMaxCols * kWave * pl.waves));

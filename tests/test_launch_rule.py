@@ -42,3 +42,26 @@ def test_tall_tiles_keep_their_slices():
     L = celty.celty_launch(0, 8, 0, 0)
     assert celty._plan(ctypes.byref(d), ctypes.byref(L), ctypes.byref(out), ctypes.byref(n), None) == celty.CELTY_OK
     assert (out.cols_per_block, n.value) == (239, 378)
+
+
+def _cut(M, K, groups, R=None, launch=None, layout=celty.LAYOUT_RLC, nnz=0):
+    """(columns, wavefronts, workgroups) of the plan."""
+    R = R or celty.default_tile_rows(M, K)
+    d = celty.celty_rlc_csc(2, M, K, R, -(-M // R), 4, groups, nnz, nnz, 0, 1.0, layout, FAKE, FAKE, FAKE, FAKE)
+    out, n = celty.celty_launch(), ctypes.c_int64()
+    L = None if launch is None else ctypes.byref(celty.celty_launch(*launch))
+    assert celty._plan(ctypes.byref(d), L, ctypes.byref(out), ctypes.byref(n), None) == celty.CELTY_OK
+    return out.cols_per_block, out.waves_per_block, n.value
+
+
+# the stored groups of uniform masks at weight sparsities of 90 and 95 %, and of 97.5 % in the fourth
+@pytest.mark.parametrize("M,K,groups,cols,blocks", [
+    (6732, 10452, 1136000, 320, 462),   # ws 90: near two per unit, not cut to something uneven between
+    (5838, 15932, 1096000, 384, 504),   # ws 95: nor to more than one column per lane
+    (4636, 15004, 826000, 320, 470),
+    (1000, 40000, 250000, 640, 252),    # slices of several columns per lane already: kept
+    (624, 23864, 184000, 508, 141),     # the fewest slices with one column per lane
+    (953, 11184, 129000, 350, 128),
+])
+def test_light_slices_stay_within_one_per_unit_and_one_column_per_lane(M, K, groups, cols, blocks):
+    assert _cut(M, K, groups) == (cols, 8, blocks)
