@@ -1371,8 +1371,25 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
   pl.T = W->T;
   // automatic shape: 16 wavefronts per compute unit on 256 compute units,
   // as one workgroup of 16 (tiles of 1024 rows or more) or two of 8
-  pl.waves = (cfg && cfg->waves_per_block) ? cfg->waves_per_block : (W->R >= 1024 ? 16 : 8);
+  const bool auto_waves = !cfg || !cfg->waves_per_block;
+  pl.waves = auto_waves ? (W->R >= 1024 ? 16 : 8) : cfg->waves_per_block;
   if (pl.waves != 2 && pl.waves != 4 && pl.waves != 8 && pl.waves != 16) return CELTY_EINVAL;
+  // one group per lane per pass unless asked otherwise: with several, the
+  // lanes of one LDS add instruction land G groups apart, which costs more
+  // bank conflicts than the bookkeeping it saves
+  pl.groups = (cfg && cfg->groups_per_lane) ? cfg->groups_per_lane : 1;
+  if (pl.groups != 1 && pl.groups != 2 && pl.groups != 4) return CELTY_EINVAL;
+  // the variant: the layout's row encoding, or the swizzled tile (RLC only);
+  // all but the plain RLC kernel take one group per lane
+  const int swz = cfg ? cfg->lds_swizzle : 0;
+  if (swz != 0 && swz != 1) return CELTY_EINVAL;
+  if (W->layout == CELTY_LAYOUT_RLC)
+    pl.var = swz ? kVarSwizzle : kVarRlc;
+  else if (swz)
+    return CELTY_EINVAL;
+  else
+    pl.var = W->layout == CELTY_LAYOUT_ROWS16 ? kVarRows16 : kVarInterleaved;
+  if (pl.var != kVarRlc && pl.groups != 1) return CELTY_EINVAL;
   int Kc = cfg ? cfg->cols_per_block : 0;
   if (Kc == 0) {
     // about 4096 / waves workgroups (16 wavefronts on each of 256 compute
@@ -1403,13 +1420,26 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     const bool dense = stored >= 15.0 / 16.0 * 2.5 * static_cast<double>(W->M) * static_cast<double>(W->K);
     const bool uneven = pl.waves == 8 && n_wg > 256 && 10 * n_wg < 9 * slots;
     const bool low = pl.waves == 8 && W->R < 1024;
-    if (low && n_wg > 256 && !dense && (W->K + k1 - 1) / k1 <= kWave * pl.waves) {
+    // The other walks: four groups per lane lose by one workgroup per unit on
+    // some shapes and two by the cut of light slices, so these keep the count
+    // (us with four at two -> one per unit: 7168 x 7168 50/50 16.17 -> 16.64,
+    // 5120 x 5120 30/30 15.33 -> 15.89; with two, uncut -> cut: 4096 x 4096
+    // 80/0 6.11 -> 6.86).  The interleaved layout gives the RLC layout's y and
+    // so takes its slices; its walk needs 16 wavefronts per unit, so where the
+    // plain kernel leaves out the second workgroup of 8 it has one of 16 (two
+    // of 8, one of 8, one of 16: 7168 x 7168 50/50 19.1, 22.0, 18.1; 4096 x
+    // 11008 18.4, 19.8, 16.4; 5003 x 3001 60/50 7.77, 7.89, 7.89).
+    const bool interleaved = pl.var == kVarInterleaved;
+    const bool one_per_unit = low && pl.groups <= 2 && (auto_waves || !interleaved);
+    const int64_t lanes = static_cast<int64_t>(kWave) * pl.waves;
+    if (uneven && stored < 80.0 * 1024.0 * static_cast<double>(W->T * ks)) {
       kc = (W->K + k1 - 1) / k1;
-    } else if (n_wg > slots || (uneven && stored >= 80.0 * 1024.0 * static_cast<double>(W->T * ks))) {
+    } else if (one_per_unit && n_wg > 256 && !dense && (W->K + k1 - 1) / k1 <= lanes) {
+      kc = (W->K + k1 - 1) / k1;
+      if (interleaved) pl.waves = 16;
+    } else if (n_wg > slots || uneven) {
       kc = (W->K + ks - 1) / ks;
-    } else if (uneven) {
-      kc = (W->K + k1 - 1) / k1;
-    } else if (low && n_wg > 128 && n_wg <= 256 && kc <= kWave * pl.waves &&
+    } else if (low && pl.groups == 1 && n_wg > 128 && n_wg <= 256 && kc <= lanes &&
                stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
       // up to one workgroup per unit the count is kept, unless a workgroup
       // would hold less than 112 bytes of stored groups for each ticket of
@@ -1427,7 +1457,6 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
       // 50 250 -> 180 -> 130 workgroups 5.03, 4.96, 5.33, 6000 x 4000 ws 80
       // 252 -> 180 5.07 -> 5.38.
       const int64_t n = std::max<int64_t>(128, static_cast<int64_t>(stored / (112.0 * static_cast<double>(W->R))));
-      const int64_t lanes = static_cast<int64_t>(kWave) * pl.waves;
       const int64_t k = std::max<int64_t>({1, n / W->T, (W->K + lanes - 1) / lanes});
       kc = (W->K + k - 1) / k;
     }
@@ -1440,22 +1469,6 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
   pl.Kc = Kc;
   pl.KC = (W->K + Kc - 1) / Kc;
   if (pl.KC > kMaxSlices) return CELTY_EINVAL;
-  // one group per lane per pass unless asked otherwise: with several, the
-  // lanes of one LDS add instruction land G groups apart, which costs more
-  // bank conflicts than the bookkeeping it saves
-  pl.groups = (cfg && cfg->groups_per_lane) ? cfg->groups_per_lane : 1;
-  if (pl.groups != 1 && pl.groups != 2 && pl.groups != 4) return CELTY_EINVAL;
-  // the variant: the layout's row encoding, or the swizzled tile (RLC only);
-  // all but the plain RLC kernel take one group per lane
-  const int swz = cfg ? cfg->lds_swizzle : 0;
-  if (swz != 0 && swz != 1) return CELTY_EINVAL;
-  if (W->layout == CELTY_LAYOUT_RLC)
-    pl.var = swz ? kVarSwizzle : kVarRlc;
-  else if (swz)
-    return CELTY_EINVAL;
-  else
-    pl.var = W->layout == CELTY_LAYOUT_ROWS16 ? kVarRows16 : kVarInterleaved;
-  if (pl.var != kVarRlc && pl.groups != 1) return CELTY_EINVAL;
   if (W->R > kMaxLds / 4) return CELTY_EINVAL;   // keeps the layout arithmetic in int
   pl.lds = static_cast<size_t>(lds_layout(W->R, pl.Kc, pl.waves, scr_words_of(pl.groups, pl.var)).bytes);
   if (pl.lds > static_cast<size_t>(kMaxLds)) return CELTY_EINVAL;
@@ -1682,14 +1695,17 @@ extern "C" celty_status celty_spmspv_batch(int32_t n, const celty_rlc_csc* const
   if (n < 1 || n > kMaxBatch || !W || !x || !tau || !y) return CELTY_EINVAL;
   for (int i = 0; i < n; ++i)
     if (celty_status st = check_header(W[i])) return st;
-  // one wavefront count and group count for the whole launch
+  // one wavefront count and group count for the whole launch (a single
+  // product's is its plan's)
   Launch ln;
   if (launch_cfg && launch_cfg->waves_per_block) {
     ln.waves = launch_cfg->waves_per_block;
-  } else {
+  } else if (n > 1) {
     ln.waves = 8;
     for (int i = 0; i < n; ++i)
       if (W[i]->R >= 1024) ln.waves = 16;
+  } else {
+    ln.waves = 0;
   }
   ln.groups = (launch_cfg && launch_cfg->groups_per_lane) ? launch_cfg->groups_per_lane : 1;
   const celty_launch cfg{launch_cfg ? launch_cfg->cols_per_block : 0, ln.waves, ln.groups,
@@ -1707,6 +1723,7 @@ extern "C" celty_status celty_spmspv_batch(int32_t n, const celty_rlc_csc* const
     if (celty_status st = make_plan(W[i], &cfg, pl)) return st;
     // the swizzled tile and the other layouts run one product per launch
     if (n > 1 && pl.var != kVarRlc) return CELTY_EINVAL;
+    ln.waves = pl.waves;
     ln.var = pl.var;
     void* ws_i = static_cast<unsigned char*>(workspace) + ws_off;
     if (celty_status st = product_args(W[i], pl, x[i], tau[i], y[i], ws_i, ba.prod[i])) return st;

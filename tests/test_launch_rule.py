@@ -65,3 +65,25 @@ def _cut(M, K, groups, R=None, launch=None, layout=celty.LAYOUT_RLC, nnz=0):
 ])
 def test_light_slices_stay_within_one_per_unit_and_one_column_per_lane(M, K, groups, cols, blocks):
     assert _cut(M, K, groups) == (cols, 8, blocks)
+
+
+@pytest.mark.parametrize("M,K,density,layout,launch,want", [
+    # two groups per lane: one workgroup per unit, no light cut; four: neither
+    (7168, 7168, 0.5, celty.LAYOUT_RLC, (0, 0, 2, 0), (399, 8, 252)),
+    (4096, 4096, 0.2, celty.LAYOUT_RLC, (0, 0, 2, 0), (128, 8, 256)),
+    (7168, 7168, 0.5, celty.LAYOUT_RLC, (0, 0, 4, 0), (200, 8, 504)),
+    (4096, 4096, 0.2, celty.LAYOUT_RLC, (0, 0, 4, 0), (128, 8, 256)),
+    # the swizzled tile and the 16-bit rows: as the plain kernel
+    (7168, 7168, 0.5, celty.LAYOUT_RLC, (0, 0, 0, 1), (399, 8, 252)),
+    (7168, 7168, 0.5, celty.LAYOUT_ROWS16, (0, 0, 0, 0), (399, 8, 252)),
+    # interleaved: the plain kernel's slices (so the same y), with 16 wavefronts
+    # where the plain kernel gives up the second workgroup
+    (7168, 7168, 0.5, celty.LAYOUT_INTERLEAVED, (0, 0, 0, 0), (399, 16, 252)),
+    (7168, 7168, 0.5, celty.LAYOUT_INTERLEAVED, (0, 8, 0, 0), (200, 8, 504)),
+    (4096, 11008, 0.5, celty.LAYOUT_INTERLEAVED, (0, 0, 0, 0), (344, 16, 256)),
+    (5120, 5120, 0.4, celty.LAYOUT_INTERLEAVED, (0, 0, 0, 0), (205, 8, 250)),
+    (4096, 4096, 0.5, celty.LAYOUT_INTERLEAVED, (0, 0, 0, 0), (128, 8, 256)),
+    (8192, 8192, 0.5, celty.LAYOUT_INTERLEAVED, (0, 0, 0, 0), (256, 16, 256)),
+])
+def test_slices_of_the_other_walks(M, K, density, layout, launch, want):
+    assert _cut(M, K, int(M * K * density) // 8, layout=layout, launch=launch) == want
