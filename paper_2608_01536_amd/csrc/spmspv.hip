@@ -1366,6 +1366,23 @@ celty_status check_header(const celty_rlc_csc* W) {
   return CELTY_OK;
 }
 
+// Bytes of groups that the RLC layout would store if W's weights were spread
+// evenly: n_nnz weights, a padding entry for every 16 zeros of a gap (gaps of
+// at least 16 j zeros: a share q^16j of them, q the share of zeros) and 3.5
+// alignment entries a segment.  A rule that chooses slices by it chooses the
+// same ones in every layout (the groups actually stored differ, the 16-bit
+// rows having no padding entries), hence the same grids and the same y.  (By
+// the weights alone the line of the light slices moves by 3 to 10 %:
+// 4096 x 4096 ws 80 as 0 6.06 -> 6.50, 2048 x 2048 ws 50 as 0 4.80 -> 5.23.)
+// A header without the count (a plan may be asked for before) takes n_groups.
+double even_rlc_bytes(const celty_rlc_csc* W) {
+  if (W->n_nnz <= 0) return 20.0 * static_cast<double>(W->n_groups);
+  const double nnz = static_cast<double>(W->n_nnz);
+  const double q = std::max(0.0, 1.0 - nnz / (static_cast<double>(W->M) * static_cast<double>(W->K)));
+  const double q2 = q * q, q4 = q2 * q2, q8 = q4 * q4, q16 = q8 * q8;
+  return 2.5 * (nnz * (1.0 + q16 / (1.0 - q16)) + 3.5 * static_cast<double>(W->T) * static_cast<double>(W->K));
+}
+
 celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl) {
   if (celty_status st = check_header(W)) return st;
   pl.T = W->T;
@@ -1440,10 +1457,10 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     } else if (n_wg > slots || uneven) {
       kc = (W->K + ks - 1) / ks;
     } else if (low && pl.groups == 1 && n_wg > 128 && n_wg <= 256 && kc <= lanes &&
-               stored < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
+               even_rlc_bytes(W) < 112.0 * static_cast<double>(W->R) * static_cast<double>(n_wg)) {
       // up to one workgroup per unit the count is kept, unless a workgroup
-      // would hold less than 112 bytes of stored groups for each ticket of
-      // its merge: then fewer, down to the whole slices of 128, as long as
+      // would hold less than 112 bytes of stored groups (as even_rlc_bytes
+      // counts them) for each ticket of its merge: then fewer, down to the whole slices of 128, as long as
       // every lane of the selection keeps to one column.  Kept count -> this
       // one, us at as 0, 50, 90: 4096 x 4096 ws 70 6.44 -> 6.39, 5.57 -> 5.44,
       // 4.86 -> 4.70; 2048 x 2048 ws 80 4.33 -> 4.31, 4.32 -> 4.01, 4.28 ->
@@ -1456,7 +1473,7 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
       // their own (the first branch) are not cut further: 5003 x 3001 ws 80 as
       // 50 250 -> 180 -> 130 workgroups 5.03, 4.96, 5.33, 6000 x 4000 ws 80
       // 252 -> 180 5.07 -> 5.38.
-      const int64_t n = std::max<int64_t>(128, static_cast<int64_t>(stored / (112.0 * static_cast<double>(W->R))));
+      const int64_t n = std::max<int64_t>(128, static_cast<int64_t>(even_rlc_bytes(W) / (112.0 * static_cast<double>(W->R))));
       const int64_t k = std::max<int64_t>({1, n / W->T, (W->K + lanes - 1) / lanes});
       kc = (W->K + k - 1) / k;
     }

@@ -117,6 +117,19 @@ def test_variant_full_size_in_the_automatic_shape(celty, torch_dev, variant, M, 
 
 
 @pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("M,K,ws,as_", [(4096, 4096, 80, 70), (5003, 3001, 60, 50)])
+def test_variant_matches_rlc_in_the_automatic_shapes_of_low_tiles(celty, torch_dev, variant, M, K, ws, as_):
+    # light slices, chosen by a count that may not depend on the layout; and
+    # one workgroup per compute unit, of 16 wavefronts for the interleaved layout
+    _note(f"{variant} automatic shape {M}x{K} ws{ws} as{as_}")
+    p = workloads.make_problem(2, M, K, ws, as_, "laplace", seed=1, proj=workloads.PROJ_IDS["w"])
+    y, y0 = _both(celty, torch_dev, variant, p.W, p.mask, p.x, p.tau, celty.default_tile_rows(M, K))
+    assert np.array_equal(y, y0), f"{int(np.count_nonzero(y != y0))} rows differ from the RLC kernel"
+    want = ref.spmspv_dense_fp64(p.W, p.mask, p.x, p.tau)
+    assert ref.rel_error(y.view(np.float16).astype(np.float64), want) <= TOL
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
 @pytest.mark.parametrize("mode", ["tau_negative", "nan_x", "all_inactive"])
 def test_variant_special_activations(celty, torch_dev, variant, mode):
     _note(f"{variant} {mode}")

@@ -4,6 +4,7 @@ lane, two per unit where it would have more or where nothing is pruned, and
 fewer than one where a workgroup holds little for its merge."""
 import ctypes
 
+import numpy as np
 import pytest
 
 import paper_2608_01536_amd as celty
@@ -87,3 +88,17 @@ def test_light_slices_stay_within_one_per_unit_and_one_column_per_lane(M, K, gro
 ])
 def test_slices_of_the_other_walks(M, K, density, layout, launch, want):
     assert _cut(M, K, int(M * K * density) // 8, layout=layout, launch=launch) == want
+
+
+@pytest.mark.parametrize("M,K,ws", [(4096, 4096, 80), (4096, 4096, 70), (3001, 1003, 75), (2048, 2048, 60)])
+def test_light_slices_are_the_same_in_every_layout(M, K, ws):
+    # a layout's stored groups depend on its padding and alignment; the slices
+    # set the grids, and with them y's last bits, so they may not
+    rng = np.random.default_rng(M + K + ws)
+    W = (rng.standard_normal((M, K), dtype=np.float32) * 0.02).astype(np.float16)
+    mask = (rng.random((M, K), dtype=np.float32) >= ws / 100).astype(np.uint8)
+    cuts = set()
+    for layout in (celty.LAYOUT_RLC, celty.LAYOUT_ROWS16, celty.LAYOUT_INTERLEAVED):
+        groups, nnz, _ = celty.celty_encode_plan(W, mask, celty.default_tile_rows(M, K), layout)
+        cuts.add(_cut(M, K, groups, layout=layout, nnz=nnz))
+    assert len(cuts) == 1, cuts
