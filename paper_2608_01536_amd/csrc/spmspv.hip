@@ -1019,8 +1019,12 @@ __device__ __forceinline__ void spmspv_block(const Early& e, const KernelArgs& p
   // A ring of DEPTH passes is kept in flight: after a pass is decoded and
   // accumulated, its slot is refilled with the loads of the pass DEPTH ahead.
   // The ring is indexed by compile-time constants (fully unrolled), so no
-  // register copies force an early wait.  Passes past the end are idle (every
-  // lane inactive, loads of group 0) and accumulate nothing.
+  // register copies force an early wait.  With one group per lane nothing is
+  // refilled past the walk's last round, and a pass of that round past the
+  // end reads past the arrays (zeros, no traffic).  The walks with several
+  // groups per lane and of the interleaved layout refill to the end; their
+  // passes past it are idle (every lane inactive, loads of group 0).  Either
+  // way they accumulate nothing.
   constexpr uint32_t P = kWave * G;
   // Wavefront wv walks the flat groups [pb0, pe), starting in segment
   // i_begin.  Segments past the range are never assigned to a live lane, so
@@ -1386,8 +1390,9 @@ double even_rlc_bytes(const celty_rlc_csc* W) {
 celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl) {
   if (celty_status st = check_header(W)) return st;
   pl.T = W->T;
-  // automatic shape: 16 wavefronts per compute unit on 256 compute units,
-  // as one workgroup of 16 (tiles of 1024 rows or more) or two of 8
+  // automatic shape: workgroups of 16 wavefronts, one on each of 256 compute
+  // units, on tiles of 1024 rows or more; on lower ones workgroups of 8, two
+  // per unit, one or fewer by the rules below
   const bool auto_waves = !cfg || !cfg->waves_per_block;
   pl.waves = auto_waves ? (W->R >= 1024 ? 16 : 8) : cfg->waves_per_block;
   if (pl.waves != 2 && pl.waves != 4 && pl.waves != 8 && pl.waves != 16) return CELTY_EINVAL;
@@ -1409,7 +1414,7 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
   if (pl.var != kVarRlc && pl.groups != 1) return CELTY_EINVAL;
   int Kc = cfg ? cfg->cols_per_block : 0;
   if (Kc == 0) {
-    // about 4096 / waves workgroups (16 wavefronts on each of 256 compute
+    // from about 4096 / waves workgroups (16 wavefronts on each of 256 compute
     // units): T row tiles times KC slices (at most 63, the merge's count
     // byte) of a multiple of 64 columns
     const int64_t slots = 4096 / pl.waves;
@@ -1418,19 +1423,24 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     const int64_t n_wg = W->T * ((W->K + kc - 1) / kc);
     // Counts past the slots start a second round.  8-wavefront counts past
     // one per compute unit (on the tiles that take 8 by themselves, under 1024
-    // rows) take one per unit where such a slice still gives
-    // every lane of the selection at most one column: the merge tickets (16
-    // bytes per row and slice) halve, and each wavefront's longer walk costs
-    // less than the second workgroup's prologue (us per product, graph of 60,
-    // two per unit -> one: 4096 x 11008 50/50 9.50 -> 9.12, 30/30 14.0 ->
-    // 13.5, 7168 x 7168 30/30 15.2 -> 14.6, 5003 x 3001 60/50 6.07 -> 5.61,
-    // 5120 x 12800 50/50 12.16 -> 12.26 the other way, the one such of 30).
+    // rows) take one per unit where such a slice still gives every lane of
+    // the selection at most one column: the merge tickets (16 bytes per row
+    // and slice) halve, and each wavefront's longer walk costs less than the
+    // second workgroup's prologue (us per product, graph of 45, two per unit
+    // -> one: 4096 x 11008 50/50 9.50 -> 9.12, 30/30 14.0 -> 13.5, 7168 x 7168
+    // 30/30 15.2 -> 14.6, 5003 x 3001 60/50 6.07 -> 5.61; of 35 shapes three
+    // lose, 5120 x 12800 50/50 the most, 12.16 -> 12.26).
     // Wider slices, with several columns per lane, keep two per unit (5120 x
     // 13824 60/60 10.3 against 11.6) in the most slices that fit the slots
     // or, between one and 0.9 x two per unit, one per unit when the slices
     // are light (under 80 KB of stored groups each at two per unit).  A
     // matrix that stores all but 1/16 of its weights is not pruned; it keeps
-    // two per unit as well (5120 x 5120 ws 0 as 50: 11.53 against 11.46).
+    // two per unit as well: one would give the plain kernel -4 to +2 % on
+    // seven shapes (5120 x 5120 ws 0 as 50 11.29 -> 11.39, 7168 x 7168 18.53
+    // -> 18.16, 4096 x 11008 ws 2 14.03 -> 13.47, 5003 x 3001 ws 0 8.22 ->
+    // 8.36), but the swizzled tile, whose y and so whose slices are the same,
+    // up to 12 % more (9.43 -> 10.21, 14.68 -> 16.44, 14.45 -> 14.21, 7.49 ->
+    // 7.59).
     const int64_t ks = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, slots / W->T));
     const int64_t k1 = std::min<int64_t>(kMaxSlices, std::max<int64_t>(1, 256 / W->T));
     const double stored = 20.0 * static_cast<double>(W->n_groups);   // bytes of groups
@@ -1438,14 +1448,18 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     const bool uneven = pl.waves == 8 && n_wg > 256 && 10 * n_wg < 9 * slots;
     const bool low = pl.waves == 8 && W->R < 1024;
     // The other walks: four groups per lane lose by one workgroup per unit on
-    // some shapes and two by the cut of light slices, so these keep the count
-    // (us with four at two -> one per unit: 7168 x 7168 50/50 16.17 -> 16.64,
-    // 5120 x 5120 30/30 15.33 -> 15.89; with two, uncut -> cut: 4096 x 4096
-    // 80/0 6.11 -> 6.86).  The interleaved layout gives the RLC layout's y and
-    // so takes its slices; its walk needs 16 wavefronts per unit, so where the
+    // some shapes and both two and four by the cut of light slices, so these
+    // keep the count (us with four at two -> one per unit: 7168 x 7168 50/50
+    // 16.17 -> 16.64, 5120 x 5120 30/30 15.33 -> 15.89; with two, uncut -> cut:
+    // 4096 x 4096 80/0 6.11 -> 6.86; two at one per unit gain on eight of nine
+    // shapes, 4096 x 11008 50/50 11.7 -> 10.2, and lose on 5003 x 3001 60/0,
+    // 7.75 -> 8.04).  The interleaved layout gives the RLC layout's y and so
+    // takes its slices; its walk needs 16 wavefronts per unit, so where the
     // plain kernel leaves out the second workgroup of 8 it has one of 16 (two
     // of 8, one of 8, one of 16: 7168 x 7168 50/50 19.1, 22.0, 18.1; 4096 x
-    // 11008 18.4, 19.8, 16.4; 5003 x 3001 60/50 7.77, 7.89, 7.89).
+    // 11008 18.4, 19.8, 16.4; 5003 x 3001 60/50 7.77, 7.89, 7.89).  Of light
+    // slices it takes the plain kernel's too, 0.92 to 1.05 of its time uncut
+    // with sparse activations and up to 1.24 without (4096 x 4096 80/0).
     const bool interleaved = pl.var == kVarInterleaved;
     const bool one_per_unit = low && pl.groups <= 2 && (auto_waves || !interleaved);
     const int64_t lanes = static_cast<int64_t>(kWave) * pl.waves;
