@@ -1,8 +1,11 @@
 """GPU parity of the one-group-per-lane walk at the sizes where its bookkeeping
 can go wrong: segments found from head bits (64 heads in a pass, heads on a
 pass's first and last position, more than 64 segments in one build of the
-bits, walks longer than one build), ranges that start inside a segment, and
-walks of one pass, of the ring's depth and of one more.
+bits, walks longer than one build, more than 64 heads left for the next
+build), ranges that start inside a segment, and walks of one pass, of the
+ring's depth and of one more, in the ring of three passes and in that of two.
+Which ring a case takes and what it leaves for a second build are computed
+from the encoded matrix and asserted.
 
 The kernels with several groups per lane find their segments another way and
 sum the same products on the same grids, so y must agree bit for bit; it is
@@ -18,6 +21,8 @@ pytestmark = pytest.mark.gpu
 
 TOL = 2e-3
 
+BUILD = 30   # passes whose heads are marked in one build
+
 # label, M, K, ws, as, R, cols, waves
 CASES = [
     ("one_group", 8, 1, 0, 0, 8, 1, 2),
@@ -31,9 +36,41 @@ CASES = [
     ("builds_of_short_segments", 96, 4096, 0, 0, 16, 1024, 2),  # 2 groups per segment, 16 passes
     ("builds_of_short_segments_long", 32, 4096, 0, 0, 32, 1024, 2),
     ("depth_and_one_more", 2048, 64, 0, 50, 1024, 64, 16),
-    ("two_pass_ring", 5120, 2000, 50, 30, 512, 40, 8),          # over 256 workgroups of 8 wavefronts
+    ("many_workgroups", 5120, 2000, 50, 30, 512, 40, 8),        # over 256 of 8 wavefronts, 2 passes each
+    ("second_build_of_many_heads", 96, 2048, 0, 0, 48, 1024, 2),
+    ("two_pass_ring", 4090, 2203, 0, 0, 512, 67, 8),
+    ("two_pass_ring_ragged", 4333, 4100, 40, 30, 509, 141, 8),
+    ("two_pass_ring_second_build", 12336, 2700, 0, 0, 48, 2700, 8),
     ("wide_slices", 1024, 6000, 60, 40, 256, 4096, 8),          # 8 columns per lane in the selection
 ]
+
+
+def ring_depth(celty, enc, launch):
+    """Passes in flight of a launch with one group per lane: two where over 256
+    workgroups of 8 wavefronts walk an estimated 4 to 16 passes each (half of
+    the stored groups taken as active), else three."""
+    plan = celty.celty_spmspv_plan(enc, launch)
+    passes = 0.5 * enc.n_groups / (plan["blocks"] * plan["waves_per_block"] * 64)
+    return 2 if plan["waves_per_block"] == 8 and plan["blocks"] > 256 and 4 <= passes <= 16 else 3
+
+
+def heads_of_later_builds(enc, x, tau, cols, waves):
+    """The most segments that start in a wavefront's range past its first
+    build (equal ranges: fewer than 16 wavefronts)."""
+    assert waves < 16
+    xf = np.abs(np.asarray(x, dtype=np.float32))
+    counts = np.diff(enc.gptr.astype(np.int64)).reshape(enc.T, enc.K) * (xf > np.float32(tau))
+    most = 0
+    for t in range(enc.T):
+        for k0 in range(0, enc.K, cols):
+            c = counts[t, k0:k0 + cols]
+            ends = np.cumsum(c[c > 0])
+            starts = ends - c[c > 0]
+            n = int(ends[-1]) if len(ends) else 0
+            for w in range(waves):
+                lo, hi = w * n // waves + 64 * BUILD, (w + 1) * n // waves
+                most = max(most, int(np.count_nonzero((starts > lo) & (starts < hi))))
+    return most
 
 
 @pytest.mark.parametrize("label,M,K,ws,as_,R,cols,waves", CASES, ids=[c[0] for c in CASES])
@@ -45,7 +82,11 @@ def test_walk(label, M, K, ws, as_, R, cols, waves):
     print(f"walk {label}", flush=True)
     dev = torch.device("cuda:0")
     p = workloads.random_small(9000 + len(label), M, K, ws=ws, as_=as_)
-    W = celty.celty_encode(p.W, p.mask, R).to_device(dev)
+    enc = celty.celty_encode(p.W, p.mask, R)
+    assert ring_depth(celty, enc, (cols, waves, 1)) == (2 if label.startswith("two_pass_ring") else 3)
+    if "second_build" in label:
+        assert heads_of_later_builds(enc, p.x, p.tau, cols, waves) > (64 if "many_heads" in label else 0)
+    W = enc.to_device(dev)
     x = torch.from_numpy(np.ascontiguousarray(p.x).view(np.int16)).to(dev)
     wsp = celty.new_workspace(W, dev)
     out = {}
