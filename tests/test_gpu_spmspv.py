@@ -881,3 +881,21 @@ def test_prepared_call_matches_spmspv_ex(celty, torch_dev):
         celty.PreparedSpMSpV(Wd, xt[:-1], y2, ws2)       # short x is refused once, here
     with pytest.raises(celty.CeltyError):
         prep(float("nan"))                                # the C entry point still validates tau
+
+
+def test_batch_of_more_workgroups_than_a_grid_row(celty, torch_dev):
+    # 2,100,003 workgroups (one row and one column each): a batch of more than
+    # 2^21 goes on in a second grid row, whose first workgroups are the second
+    # product's and whose last ones have nothing to do; single-term rows, bit-exact
+    _note("batch of 1100000 + 1000003 workgroups")
+    rng = np.random.default_rng(77)
+    probs = []
+    for M, x in ((1100000, 1.5), (1000003, -0.37)):
+        W = workloads.draw_weight(rng, M, 1)
+        W[rng.integers(0, M, size=1000), 0] = 0
+        probs.append(workloads.Problem(W, None, np.array([x], np.float16), 0.1, {}))
+    yb, ys = _batch_run(celty, torch_dev, probs, [1, 1], (1, 2, 1))
+    for p, a, b in zip(probs, yb, ys):
+        want = np.where(p.W[:, 0] == 0, np.float32(0), p.W[:, 0].astype(np.float32) * np.float32(p.x[0])).astype(np.float16)
+        assert np.array_equal(a.view(np.uint16), want.view(np.uint16))
+        assert np.array_equal(b.view(np.uint16), want.view(np.uint16))
