@@ -178,11 +178,16 @@ celty_status celty_select(const void* x, int32_t K, float tau, int32_t* idx, int
                           void* stream);
 
 /* Launch shape of celty_spmspv_ex.  Zero fields mean "choose automatically":
- * 16 wavefronts per workgroup for R >= 1024, else 8; slices sized for about
- * 4096 / waves_per_block workgroups (16 wavefronts on each of 256 compute
- * units), never more; 8-wavefront workgroups are one per unit where a slice
- * then has at most 512 columns, and fewer where a slice would be light for
- * its merge; one group per lane.  The K columns are cut into
+ * one group per lane; for R >= 1024 workgroups of 16 wavefronts, one on each
+ * of 256 compute units; for lower tiles workgroups of 8, one per unit where a
+ * slice then has at most 512 columns, fewer (the whole slices in 128, or more)
+ * where it would still be light for its merge, and two per unit where it would be wider or
+ * where less than 1/16 of the weights is pruned.  Slices are the same for every
+ * layout, except that a wide, light ROWS16 matrix may take one workgroup per
+ * unit where its RLC form takes two; INTERLEAVED takes 16 wavefronts where the
+ * rule gives a low tile one workgroup per unit instead of two, and 8 given
+ * explicitly keep the two; with 4 groups per lane the rules for low tiles do
+ * not apply, with 2 the one for light slices does not.  The K columns are cut into
  * ceil(K / cols_per_block) slices, at most 63 (the merge counts 6-bit
  * arrivals in a 64-bit word).  A workgroup's lanes scan at most 8 columns
  * each: cols_per_block <= 512 * waves_per_block.
@@ -263,7 +268,7 @@ celty_status celty_spmspv_workspace_init(void* workspace, size_t workspace_bytes
  * colmax must bound every |stored value| of its column (the encoder sets it
  * exactly): a smaller value can overflow the int32 tile and give wrong rows,
  * but never an access outside the arrays.
- * Every layout gives the same y.
+ * Every layout gives the same y for the same slices (cols_per_block).
  * Errors: EINVAL (null or misaligned pointers, inconsistent header, NaN tau,
  *         non-finite or negative max_abs, short workspace, more than 63
  *         column slices, cols_per_block above 512 * waves_per_block,
@@ -295,7 +300,7 @@ celty_status celty_spmspv_ex(const celty_rlc_csc* W, const void* x, float tau, v
  *              first use and left zero-filled by every completed call.
  *   launch     as for celty_spmspv_ex; cols_per_block applies to every product,
  *              the automatic choice is made per product, with 16 wavefronts
- *              when any product has R >= 1024.
+ *              for all when any product has R >= 1024, else 8.
  * Results are those of n separate celty_spmspv_ex calls with the same launch.
  * With n > 1 every product must use CELTY_LAYOUT_RLC without lds_swizzle.
  * Errors: EINVAL (n outside 1..8, null arrays, any product's celty_spmspv

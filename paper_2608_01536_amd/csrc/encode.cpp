@@ -9,8 +9,9 @@
 // A random mask makes a branch per weight mispredict every other time, which
 // was most of the time: the counting is branch-free in 16-bit vector lanes,
 // and the fill takes each row's stored columns from a list made without
-// branches.  Plan and encode of 4096 x 4096 at 50 % weight sparsity, 8 cores:
-// 66 -> 13 ms (the plan alone 20.8 -> 1.6).
+// branches.  Plan and encode of 4096 x 4096 at 50 % weight sparsity: 14.9 ->
+// 4.6 ms on 16 cores, 70 -> 16 on 8 cores of another machine (the plan alone
+// 21.5 -> 2.1).
 //
 // Three layouts of the rows: 4-bit runs (the paper's); 16-bit row offsets
 // within the tile (no padding entries, a decode-free form); and the RLC
