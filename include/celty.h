@@ -186,8 +186,8 @@ celty_status celty_select(const void* x, int32_t K, float tau, int32_t* idx, int
  * layout, except that a wide, light ROWS16 matrix may take one workgroup per
  * unit where its RLC form takes two; INTERLEAVED takes 16 wavefronts where the
  * rule gives a low tile one workgroup per unit instead of two, and 8 given
- * explicitly keep the two; with 4 groups per lane the rules for low tiles do
- * not apply, with 2 the one for light slices does not.  The K columns are cut into
+ * explicitly keep the two; with several groups per lane the rules for low
+ * tiles do not apply.  The K columns are cut into
  * ceil(K / cols_per_block) slices, at most 63 (the merge counts 6-bit
  * arrivals in a 64-bit word).  A workgroup's lanes scan at most 8 columns
  * each: cols_per_block <= 512 * waves_per_block.

@@ -1447,21 +1447,22 @@ celty_status make_plan(const celty_rlc_csc* W, const celty_launch* cfg, Plan& pl
     const bool dense = stored >= 15.0 / 16.0 * 2.5 * static_cast<double>(W->M) * static_cast<double>(W->K);
     const bool uneven = pl.waves == 8 && n_wg > 256 && 10 * n_wg < 9 * slots;
     const bool low = pl.waves == 8 && W->R < 1024;
-    // The other walks: four groups per lane lose by one workgroup per unit on
-    // some shapes and both two and four by the cut of light slices, so these
-    // keep the count (us with four at two -> one per unit: 7168 x 7168 50/50
-    // 16.17 -> 16.64, 5120 x 5120 30/30 15.33 -> 15.89; with two, uncut -> cut:
-    // 4096 x 4096 80/0 6.11 -> 6.86; two at one per unit gain on eight of nine
-    // shapes, 4096 x 11008 50/50 11.7 -> 10.2, and lose on 5003 x 3001 60/0,
-    // 7.75 -> 8.04).  The interleaved layout gives the RLC layout's y and so
-    // takes its slices; its walk needs 16 wavefronts per unit, so where the
-    // plain kernel leaves out the second workgroup of 8 it has one of 16 (two
-    // of 8, one of 8, one of 16: 7168 x 7168 50/50 19.1, 22.0, 18.1; 4096 x
-    // 11008 18.4, 19.8, 16.4; 5003 x 3001 60/50 7.77, 7.89, 7.89).  Of light
-    // slices it takes the plain kernel's too, 0.92 to 1.05 of its time uncut
-    // with sparse activations and up to 1.24 without (4096 x 4096 80/0).
+    // The other walks.  Several groups per lane gain on most shapes by one
+    // workgroup per unit but lose on others (us, two per unit -> one: with
+    // four 7168 x 7168 50/50 16.17 -> 16.64, 5120 x 5120 30/30 15.33 -> 15.89;
+    // with two 5003 x 3001 60/0 7.75 -> 8.04, 5120 x 5120 30/0 13.45 -> 13.75),
+    // and by the cut of light slices (with two 4096 x 4096 80/0 6.11 -> 6.86),
+    // so they keep the counts without these rules.  The swizzled tile gives
+    // the plain tile's y and so takes its slices (-23 to +4 %, the most at
+    // 5120 x 5120 30/0, 12.08 -> 12.52).  So does the interleaved layout; its
+    // walk needs 16 wavefronts per unit, so where the plain kernel leaves out
+    // the second workgroup of 8 it has one of 16 (two of 8, one of 8, one of
+    // 16: 7168 x 7168 50/50 19.1, 22.0, 18.1; 4096 x 11008 18.4, 19.8, 16.4;
+    // 5003 x 3001 60/50 7.77, 7.89, 7.89).  Of light slices it takes the plain
+    // kernel's too, 0.92 to 1.05 of its time uncut with sparse activations and
+    // up to 1.24 without (4096 x 4096 80/0).
     const bool interleaved = pl.var == kVarInterleaved;
-    const bool one_per_unit = low && pl.groups <= 2 && (auto_waves || !interleaved);
+    const bool one_per_unit = low && pl.groups == 1 && (auto_waves || !interleaved);
     const int64_t lanes = static_cast<int64_t>(kWave) * pl.waves;
     if (uneven && stored < 80.0 * 1024.0 * static_cast<double>(W->T * ks)) {
       kc = (W->K + k1 - 1) / k1;

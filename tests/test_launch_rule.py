@@ -69,8 +69,8 @@ def test_light_slices_stay_within_one_per_unit_and_one_column_per_lane(M, K, gro
 
 
 @pytest.mark.parametrize("M,K,density,layout,launch,want", [
-    # two groups per lane: one workgroup per unit, no light cut; four: neither
-    (7168, 7168, 0.5, celty.LAYOUT_RLC, (0, 0, 2, 0), (399, 8, 252)),
+    # several groups per lane: neither rule
+    (7168, 7168, 0.5, celty.LAYOUT_RLC, (0, 0, 2, 0), (200, 8, 504)),
     (4096, 4096, 0.2, celty.LAYOUT_RLC, (0, 0, 2, 0), (128, 8, 256)),
     (7168, 7168, 0.5, celty.LAYOUT_RLC, (0, 0, 4, 0), (200, 8, 504)),
     (4096, 4096, 0.2, celty.LAYOUT_RLC, (0, 0, 4, 0), (128, 8, 256)),
